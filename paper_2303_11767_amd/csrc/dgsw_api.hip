@@ -319,7 +319,7 @@ int dg_set_levels(dg_ctx *ctx, int32_t n_levels) {
     return fail(DG_EUNSUPPORTED, "an ensemble member holds one layer");
   // wavefronts of one layer in either layout (the half-line layout row-aligned
   // or packed across rows), bounded so that all layers fit one launch
-  const int64_t gh = 64 / (2 * ctx->np);
+  const int64_t gh = 64 / (2 * ctx->np);   // (groups of the r = 3 FP64 stage: half as large)
   const int64_t E = (int64_t)ctx->d.n_lon * ctx->d.n_lat;
   int64_t per = (int64_t)dgsw::waves_per_row(ctx->np, ctx->d.n_lon) * ctx->d.n_lat;
   per = std::max(per, (ctx->d.n_lon + gh - 1) / gh * ctx->d.n_lat);

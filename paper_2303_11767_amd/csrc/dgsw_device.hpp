@@ -97,8 +97,12 @@ hipError_t launch_ens_stage(int dtype, int npmax, int wpb, const EnsLaunch &a, h
 // (0 line, 1 half; the items and bounds of that group).
 hipError_t launch_ens_stage_np(int dtype, int np, int layout, int wpb, const EnsLaunch &a, hipStream_t s);
 
-// Wavefronts (work items) of one member, and elements per wavefront.
+// Line layout: wavefronts per row.
 int waves_per_row(int np, int n_lon);
+// Half layout: elements of one wavefront (r = 3 in FP64: of one group of the
+// matrix-core stage, dgsw_stage_m4.hpp).
+constexpr int kM4Elems = 4;
+inline int half_elems(int dtype, int np) { return dtype == 0 && np == 4 ? kM4Elems : 64 / (2 * np); }
 
 // Upload helpers: convert FP64 host tables to the device layouts.
 // Returns the number of bytes of each table for (dtype, np).

@@ -1,6 +1,7 @@
 // Ensemble stage kernels: many meshes of different size and order in one
 // launch per stage (or one per order); the stage itself is in dgsw_stage.hpp.
 #include "dgsw_stage.hpp"
+#include "dgsw_stage_m4.hpp"
 
 namespace dgsw {
 
@@ -112,9 +113,11 @@ __device__ __forceinline__ StageArgs<T, NP> ens_args(const EnsItem &m, const uns
 // LDS of one wavefront per layout: the line and half variants
 template <typename T, int NP, int LAY>
 struct EnsLds {
-  static constexpr int TB = LAY == 0 ? Shape<T, NP>::TB : ShapeH2<T, NP>::TB;
-  static constexpr int SH = LAY == 0 ? (Shape<T, NP>::GPW + 1) * Shape<T, NP>::SH
-                                     : ShapeH2<T, NP>::SLOTS * ShapeH2<T, NP>::SH;
+  static constexpr bool G4 = M4<T, NP> && LAY == 1;
+  static constexpr int TB = G4 ? 2 : (LAY == 0 ? Shape<T, NP>::TB : ShapeH2<T, NP>::TB);
+  static constexpr int SH = G4 ? kM4Lds
+                               : (LAY == 0 ? (Shape<T, NP>::GPW + 1) * Shape<T, NP>::SH
+                                           : ShapeH2<T, NP>::SLOTS * ShapeH2<T, NP>::SH);
 };
 
 template <typename T, int NP, int LAY, int CM>
@@ -122,6 +125,9 @@ __device__ __forceinline__ void ens_item(const EnsItem &m, const unsigned char *
                                          const T *q0, T *out, int combine, T c0, T ce, int lane, T *tab, T *sh) {
   if constexpr (LAY == 0) {
     ens_case<T, NP, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh);
+  } else if constexpr (M4<T, NP>) {
+    const StageArgs<T, NP> A = ens_args<T, NP>(m, tabs, q, q0, out, combine, c0, ce);
+    m4_one<CM>(A, M4Group{m.seg, m.e_end, m.j, 0}, lane, (lds_double *)sh);
   } else {
     stage_wave_h2<T, NP, CM, true>(ens_args<T, NP>(m, tabs, q, q0, out, combine, c0, ce), m.j, m.seg, m.e_end, lane,
                                    tab, sh);
@@ -139,7 +145,7 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage_np(const T *__restrict__
                                                            const int *__restrict__ bounds, int combine,
                                                            T c0, T ce) {
   __shared__ T tab_all[WPB][EnsLds<T, NP, LAY>::TB];
-  __shared__ T sh_all[WPB][EnsLds<T, NP, LAY>::SH];
+  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY>::SH];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int part = xcd_block(blockIdx.x, gridDim.x);
   const int end = bounds[part + 1];
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage_flat(const T *__restrict
                                                              const EnsItem *__restrict__ items,
                                                              int begin, int end, int combine, T c0, T ce) {
   __shared__ T tab_all[WPB][EnsLds<T, NP, LAY>::TB];
-  __shared__ T sh_all[WPB][EnsLds<T, NP, LAY>::SH];
+  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY>::SH];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int it = begin + xcd_block(blockIdx.x, gridDim.x) * WPB + wv;
   if (it >= end) return;

@@ -103,8 +103,8 @@ int build_items(dg_ens *e) {
       for (int j = 0; j < n_lat; ++j)
         for (int sg = 0; sg < segs; ++sg) add(j, sg, 0, np3);
     } else {
-      const int gpw = 64 / (2 * c->np);
-      const double w = np3 * 0.5;
+      const int gpw = dgsw::half_elems(e->dtype, c->np);
+      const double w = np3 * 2.0 * c->np * gpw / 128.0;
       if (gpw <= n_lon && n_lon % gpw != 0) {      // packed across row ends
         for (int e0 = 0; e0 < E; e0 += gpw) add(e0 / n_lon, e0, E, w);
       } else {

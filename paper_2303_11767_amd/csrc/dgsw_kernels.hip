@@ -1,25 +1,17 @@
 // Mesh stage kernels (both layouts), mass diagnostic, launchers and the
 // upload of the tables; the stage itself is in dgsw_stage.hpp.
 #include "dgsw_stage.hpp"
+#include "dgsw_stage_m4.hpp"
 
 namespace dgsw {
 
 // PK: wavefront w of a layer takes the GPW consecutive elements from w GPW on,
 // across row ends (needs GPW <= n_lon; ceil(E / GPW) wavefronts); otherwise
-// row-aligned segments, segs per row.  One wavefront per workgroup (8960
-// bytes of LDS at FP64 r = 3: the 16 wavefronts per CU that the registers
-// allow fit).  Register budget: four wavefronts per SIMD (128 registers) at
-// FP64 r = 3 with the one-state combinations, which fit without spilling (the
-// RK4 combination would spill); two (256) elsewhere, which keeps the FP64
-// r >= 5 cases, at the edge of 256, from spilling into accumulation registers
-// and halving their occupancy.
-template <typename T, int NP, int CM>
-struct H2Occ {
-  static constexpr int value = sizeof(T) == 8 && NP == 4 && CM != 2 ? 4 : 2;
-};
-
+// row-aligned segments, segs per row.  One wavefront per workgroup.  Register budget: two wavefronts per SIMD (256 registers), which
+// keeps the FP64 r >= 5 cases, at the edge of 256, from spilling into
+// accumulation registers and halving their occupancy.
 template <typename T, int NP, int WPB, int CM, bool PK>
-__global__ __attribute__((amdgpu_waves_per_eu(H2Occ<T, NP, CM>::value))) __launch_bounds__(64 * WPB) void k_dg_stage_h2(
+__global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * WPB) void k_dg_stage_h2(
     StageArgs<T, NP> A, int segs) {
   using S_ = ShapeH2<T, NP>;
   __shared__ T tab_all[WPB][S_::TB];
@@ -43,6 +35,50 @@ __global__ __attribute__((amdgpu_waves_per_eu(H2Occ<T, NP, CM>::value))) __launc
   }
   stage_wave_h2<T, NP, CM, PK>(layer_args(A, lev), j0, e0, e_end, threadIdx.x & 63, tab_all[wv],
                                sh_all[wv]);
+}
+
+// r = 3 in FP64 (the half layout there): stage groups of four elements on the
+// matrix cores, `loop` consecutive groups per wavefront, the next one's data
+// fetched while the present one is worked on.  MORE: a forcing or the general
+// combination's extra states are read (three wavefronts per SIMD then, four
+// otherwise: the register budgets that hold without spilling).
+template <int CM, bool MORE>
+__global__ __attribute__((amdgpu_waves_per_eu(MORE ? 3 : 4))) __launch_bounds__(64) void k_dg_stage_m4(
+    StageArgs<double, 4> A, int per, int loop) {
+  __shared__ __attribute__((aligned(16))) double sh_[kM4Lds];
+  lds_double *sh = (lds_double *)sh_;
+  const int lane = threadIdx.x;
+  const int all = per * A.levels;
+  int n = xcd_block(blockIdx.x, gridDim.x) * loop;
+  const int end = n + loop < all ? n + loop : all;
+  if (n >= end) return;
+  const bool use_q0 = CM == 2 || (CM == 1 && A.c0 != 0.0);
+  auto group = [&](int m) {
+    const int lev = A.levels == 1 ? 0 : (unsigned)m / (unsigned)per;
+    return m4_group(A.n_lon, A.n_lat, m - lev * per, lev * A.lstride);
+  };
+  const M4Tab t = m4_tables(A.gt, lane);
+  M4Group g = group(n);
+  m4_fetch(A, g, use_q0, lane, sh);
+  m4_fetched();
+  for (;;) {
+    M4Data d = m4_read(A, g, use_q0, lane, sh);
+    const M4More o = m4_more<CM, MORE>(A, g, lane);
+    m4_have_read();
+    M4Group next = g;
+    ++n;
+    if (n < end) {
+      next = group(n);
+      m4_fetch(A, next, use_q0, lane, sh);
+    }
+    m4_compute<CM>(A, t, d, o, lane, sh);
+    wave_sync();
+    // the next group's data before the stores are queued behind them
+    if (n < end) m4_fetched();
+    m4_store(A, g, lane, sh);
+    if (n >= end) break;
+    g = next;
+  }
 }
 
 template <typename T, int NP, int WPB, int CM>
@@ -156,32 +192,62 @@ static StageArgs<T, NP> stage_args(const StageLaunch &a) {
   return A;
 }
 
+// Groups per wavefront: one where the mesh fills at most three wavefronts per
+// SIMD (more in flight beats the prefetch: 150x75 6.2 us a stage with one, 6.6
+// with two); then two (180x90 7.6 / 7.2 / 8.1 us with 1 / 2 / 4, 360x180 22.3 /
+// 19.9 / 20.1); four from about 25000 groups (512x256 40.4 / 36.1 / 35.2 / 38.9
+// with 1 / 2 / 4 / 6), six from 131072 (1440x720 323 / 295 / 284 / 281).
+static int m4_loop(long long groups) {
+  return groups <= 3200 ? 1 : (groups <= 24576 ? 2 : (groups <= 131072 ? 4 : 6));
+}
+
 template <typename T, int NP>
 static hipError_t launch_stage_t(const StageLaunch &a, hipStream_t s) {
   if (a.levels < 1) return hipErrorInvalidValue;
   const StageArgs<T, NP> A = stage_args<T, NP>(a);
   if (a.variant == 1) {
-    constexpr int GPW = ShapeH2<T, NP>::GPW;
-    const int segs = (a.n_lon + GPW - 1) / GPW;
-    // rows that end in a partly filled wavefront: pack the elements across
-    // row ends instead (a wavefront then spans at most two rows)
-    const bool packed = GPW <= a.n_lon && a.n_lon % GPW != 0;
-    const int per = packed ? (a.n_lon * a.n_lat + GPW - 1) / GPW : segs * a.n_lat;
-    const int waves = per * a.levels;
-    const dim3 grid(waves), block(64);
-#define DGSW_H2(CM_)                                                                      \
-  do {                                                                                    \
-    if (packed) hipLaunchKernelGGL((k_dg_stage_h2<T, NP, 1, CM_, true>), grid, block, 0, s, A, segs); \
-    else hipLaunchKernelGGL((k_dg_stage_h2<T, NP, 1, CM_, false>), grid, block, 0, s, A, segs);      \
+    if constexpr (M4<T, NP>) {
+      const int per = m4_groups(a.n_lon, a.n_lat);
+      const long long all = (long long)per * a.levels;
+      const bool more = a.forcing || (a.combine == 2 && (a.qa || a.qb));
+      const int loop = m4_loop(all);
+      const dim3 grid((unsigned)((all + loop - 1) / loop)), block(64);
+#define DGSW_M4(CM_)                                                                            \
+  do {                                                                                          \
+    if (more) hipLaunchKernelGGL((k_dg_stage_m4<CM_, true>), grid, block, 0, s, A, per, loop);  \
+    else hipLaunchKernelGGL((k_dg_stage_m4<CM_, false>), grid, block, 0, s, A, per, loop);      \
   } while (0)
-    switch (a.combine) {
-      case 0: DGSW_H2(0); break;
-      case 1: DGSW_H2(1); break;
-      case 2: DGSW_H2(2); break;
-      default:
-        return hipErrorInvalidValue;
-    }
+      switch (a.combine) {
+        case 0: DGSW_M4(0); break;
+        case 1: DGSW_M4(1); break;
+        case 2: DGSW_M4(2); break;
+        default:
+          return hipErrorInvalidValue;
+      }
+#undef DGSW_M4
+    } else {
+      constexpr int GPW = ShapeH2<T, NP>::GPW;
+      const int segs = (a.n_lon + GPW - 1) / GPW;
+      // rows that end in a partly filled wavefront: pack the elements across
+      // row ends instead (a wavefront then spans at most two rows)
+      const bool packed = GPW <= a.n_lon && a.n_lon % GPW != 0;
+      const int per = packed ? (a.n_lon * a.n_lat + GPW - 1) / GPW : segs * a.n_lat;
+      const int waves = per * a.levels;
+      const dim3 grid(waves), block(64);
+#define DGSW_H2(CM_)                                                                      \
+    do {                                                                                    \
+      if (packed) hipLaunchKernelGGL((k_dg_stage_h2<T, NP, 1, CM_, true>), grid, block, 0, s, A, segs); \
+      else hipLaunchKernelGGL((k_dg_stage_h2<T, NP, 1, CM_, false>), grid, block, 0, s, A, segs);      \
+    } while (0)
+      switch (a.combine) {
+        case 0: DGSW_H2(0); break;
+        case 1: DGSW_H2(1); break;
+        case 2: DGSW_H2(2); break;
+        default:
+          return hipErrorInvalidValue;
+      }
 #undef DGSW_H2
+    }
     return hipGetLastError();
   }
   constexpr int GPW = Shape<T, NP>::GPW;
@@ -248,6 +314,8 @@ static void fill_glob_t(const HostTables &t, double g, double radius, double ome
   G.two_href = T(2.0 * href);
   G.alpha = T(alpha);
   std::memcpy(dst, &G, sizeof(G));
+  if constexpr (M4<T, NP>)
+    m4_lane_tables(G, reinterpret_cast<double *>(static_cast<unsigned char *>(dst) + kM4TabOff));
 }
 
 template <typename T, int NP>
@@ -275,7 +343,9 @@ static void fill_rows_t(const HostTables &t, void *dst) {
 }
 
 template <typename T, int NP>
-static size_t glob_bytes_t() { return sizeof(GlobTab<T, NP>); }
+static size_t glob_bytes_t() {
+  return M4<T, NP> ? kM4GlobBytes : sizeof(GlobTab<T, NP>);
+}
 template <typename T, int NP>
 static size_t rows_bytes_t(int n_lat) { return sizeof(RowTab<T, NP>) * (size_t)n_lat; }
 template <typename T, int NP>

@@ -542,14 +542,14 @@ struct ShapeH2 {
   static constexpr int NB = 3 * (NP + 2) * NP;
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   // SPLIT: each half evaluates the node terms at its own NP / 2 nodes of a
-  // column and hands them to the other half (FP64 with an even r + 1 >= 4)
+  // column and hands them to the other half (FP64 with an even r + 1 >= 6; at
+  // r = 3 the half layout is the matrix-core stage of dgsw_stage_m4.hpp)
   static constexpr bool SPLIT = sizeof(T) == 8 && NP % 2 == 0 && NP >= 4;
   // second phase: the volume outputs [3][2][NP][NP], the longitude edge
   // fluxes of both halves [3][2][NP], and the latitude ones [3][2][NP] (oGY).
   // With SPLIT the latitude ones and then the node terms, XQ quantities
   // [XQ][NP][NP] at a time, use the region of the volume outputs first (both
-  // are read before those are written), which keeps FP64 r = 3 within the LDS
-  // of 16 wavefronts per CU.
+  // are read before those are written).
   static constexpr int oFX = 6 * NP * NP, oGY = SPLIT ? 0 : oFX + 6 * NP, XQ = 4;
   static constexpr int SH = cmax(NB + 12 * NP, oFX + (SPLIT ? 6 : 12) * NP);
   static constexpr int SLOTS = GPW + (SPARE ? 1 : 0);
@@ -632,7 +632,7 @@ __device__ __forceinline__ void stage_wave_h2(const StageArgs<T, NP> &A, const i
   using S_ = ShapeH2<T, NP>;
   constexpr int N = S_::N, GPW = S_::GPW, SH = S_::SH, NB = S_::NB, K0 = S_::K0;
   // SPLIT: each half evaluates the node terms at its own K0 nodes of the
-  // column and takes the other half's through LDS (FP64 with an even r + 1 >= 4,
+  // column and takes the other half's through LDS (FP64 with an even r + 1 >= 6,
   // where the node terms dominate and it measured faster); otherwise both
   // halves evaluate all r + 1 nodes (faster at r = 2 and 4 and in FP32)
   constexpr bool SPLIT = S_::SPLIT;
