@@ -22,13 +22,9 @@ using dgsw::kInPad;
 using dgsw::kOut;
 using dgsw::kOutPad;
 
-constexpr int64_t kParams = (int64_t)kFeatures * kHidden + kHidden + (int64_t)kHidden * kHidden + kHidden +
-                            (int64_t)kHidden * kOut + kOut;
-
-// offsets into the flat FP32 parameter vector
-constexpr int64_t oW1 = 0, ob1 = oW1 + (int64_t)kFeatures * kHidden, oW2 = ob1 + kHidden,
-                  ob2 = oW2 + (int64_t)kHidden * kHidden, oW3 = ob2 + kHidden,
-                  ob3 = oW3 + (int64_t)kHidden * kOut;
+using dgsw::kParams;
+using dgsw::ob1;
+using dgsw::ob2;
 
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -45,83 +41,54 @@ struct Carve {
   }
 };
 
-// BF16 weights for the forward pass (and the backward pass when Wr != null);
-// the hidden layers' also in the fused network kernel's fragment order
-struct Weights {
-  __bf16 *W1t, *W2t, *W3t, *W1r, *W2r, *W3r, *W1f, *W2f;
-  float *b3p;
-};
+// BF16 weights for the network kernel, or for the training step
+using Weights = dgsw::PrepWeights;
 
-Weights carve_weights(Carve &c, bool backward) {
+Weights carve_weights(Carve &c, bool train) {
   Weights w;
-  w.W1t = c.take<__bf16>((size_t)kHidden * kInPad);
-  w.W2t = c.take<__bf16>((size_t)kHidden * kHidden);
-  w.W3t = c.take<__bf16>((size_t)kOutPad * kHidden);
-  w.W1r = backward ? c.take<__bf16>((size_t)kInPad * kHidden) : nullptr;
-  w.W2r = backward ? c.take<__bf16>((size_t)kHidden * kHidden) : nullptr;
-  w.W3r = backward ? c.take<__bf16>((size_t)kHidden * kOutPad) : nullptr;
   w.W1f = c.take<__bf16>((size_t)kHidden * kInPad);
   w.W2f = c.take<__bf16>((size_t)kHidden * kHidden);
+  w.W3t = train ? nullptr : c.take<__bf16>((size_t)kOutPad * kHidden);
+  w.W3f = train ? c.take<__bf16>((size_t)kOutPad * kHidden) : nullptr;
+  w.W2rf = train ? c.take<__bf16>((size_t)kHidden * kHidden) : nullptr;
+  w.W3rf = train ? c.take<__bf16>((size_t)kHidden * kOutPad) : nullptr;
   w.b3p = c.take<float>(kOutPad);
   return w;
 }
 
-hipError_t prep(const float *P, const Weights &w, hipStream_t s) {
-  hipError_t e;
-  if ((e = dgsw::launch_prep_weights(P + oW1, kFeatures, kHidden, kInPad, kHidden, w.W1t, w.W1r, w.W1f, s)) != hipSuccess)
-    return e;
-  if ((e = dgsw::launch_prep_weights(P + oW2, kHidden, kHidden, kHidden, kHidden, w.W2t, w.W2r, w.W2f, s)) != hipSuccess)
-    return e;
-  if ((e = dgsw::launch_prep_weights(P + oW3, kHidden, kOut, kHidden, kOutPad, w.W3t, w.W3r, nullptr, s)) != hipSuccess)
-    return e;
-  return dgsw::launch_pad(P + ob3, kOut, kOutPad, w.b3p, s);
-}
-
-// Forward pass on Xb[rows][kInPad] -> Y[rows][kOutPad] (FP32), keeping the
-// pre-activations when Z1/Z2 are given.
-hipError_t forward(const float *P, const Weights &w, const __bf16 *Xb, int rows, float *Z1, __bf16 *H1, float *Z2,
-                   __bf16 *H2, float *Y, hipStream_t s) {
-  dgsw::GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.A = Xb; g.B = w.W1t; g.M = rows; g.N = kHidden; g.K = kInPad; g.lda = kInPad; g.ldb = kInPad;
-  g.bias = P + ob1; g.Zout = Z1; g.C = H1; g.ldc = kHidden;
-  hipError_t e = dgsw::launch_gemm(true, true, dgsw::kEpiBiasGelu, g, s);
-  if (e != hipSuccess) return e;
-  g.A = H1; g.B = w.W2t; g.K = kHidden; g.lda = kHidden; g.ldb = kHidden; g.bias = P + ob2; g.Zout = Z2; g.C = H2;
-  if ((e = dgsw::launch_gemm(true, true, dgsw::kEpiBiasGelu, g, s)) != hipSuccess) return e;
-  g.A = H2; g.B = w.W3t; g.N = kOutPad; g.bias = w.b3p; g.Zout = nullptr; g.C = Y; g.ldc = kOutPad;
-  return dgsw::launch_gemm(true, true, dgsw::kEpiBias, g, s);
-}
-
 struct TrainWs {
   Weights w;
-  __bf16 *Xb, *H1, *H2, *dY, *dZ2, *dZ1;
-  float *Z1, *Z2, *Y, *dYf, *dZ2f, *dZ1f, *G1, *G2, *G3, *grad, *partial, *split, *csum;
+  __bf16 *Xf, *H1f, *H2f, *DYf, *D2f, *D1f;
+  float *part, *bias_part, *se_part;
 };
 
 TrainWs carve_train(void *ws, int64_t rows, size_t *bytes) {
   Carve c(ws);
   TrainWs t;
   t.w = carve_weights(c, true);
-  t.Xb = c.take<__bf16>(rows * kInPad);
-  t.Z1 = c.take<float>(rows * kHidden);
-  t.H1 = c.take<__bf16>(rows * kHidden);
-  t.Z2 = c.take<float>(rows * kHidden);
-  t.H2 = c.take<__bf16>(rows * kHidden);
+  t.Xf = c.take<__bf16>(rows * kInPad);
+  t.H1f = c.take<__bf16>(rows * kHidden);
+  t.H2f = c.take<__bf16>(rows * kHidden);
+  t.DYf = c.take<__bf16>(rows * kOutPad);
+  t.D2f = c.take<__bf16>(rows * kHidden);
+  t.D1f = c.take<__bf16>(rows * kHidden);
+  t.part = c.take<float>((size_t)dgsw::train_splits((int)rows) * dgsw::kGradPart);
+  t.bias_part = c.take<float>((size_t)dgsw::kMaxTrainBlocks * dgsw::kBiasPart);
+  t.se_part = c.take<float>(dgsw::kMaxTrainBlocks);
+  if (bytes) *bytes = c.off;
+  return t;
+}
+
+struct ForwardWs {
+  Weights w;
+  float *Y;
+};
+
+ForwardWs carve_forward(void *ws, int64_t rows, size_t *bytes) {
+  Carve c(ws);
+  ForwardWs t;
+  t.w = carve_weights(c, false);
   t.Y = c.take<float>(rows * kOutPad);
-  t.dY = c.take<__bf16>(rows * kOutPad);
-  t.dYf = c.take<float>(rows * kOutPad);
-  t.dZ2 = c.take<__bf16>(rows * kHidden);
-  t.dZ2f = c.take<float>(rows * kHidden);
-  t.dZ1 = c.take<__bf16>(rows * kHidden);
-  t.dZ1f = c.take<float>(rows * kHidden);
-  t.G1 = c.take<float>((size_t)kInPad * kHidden);
-  t.G2 = c.take<float>((size_t)kHidden * kHidden);
-  t.G3 = c.take<float>((size_t)kHidden * kOutPad);
-  t.grad = c.take<float>(kParams);
-  t.partial = c.take<float>((rows * kOutPad + 255) / 256 + 1);
-  t.split = c.take<float>((size_t)dgsw::gemm_splits((int)rows) * kHidden * kHidden);
-  t.csum = c.take<float>((size_t)dgsw::colsum_chunks((int)rows) * kHidden);
   if (bytes) *bytes = c.off;
   return t;
 }
@@ -163,9 +130,10 @@ int dg_mlp_param_count(int64_t *n) {
 
 int dg_mlp_workspace_size(int64_t rows, int64_t *bytes) {
   if (!bytes || rows < 1) return fail(DG_EINVAL, "bad argument");
-  size_t b = 0;
-  carve_train(nullptr, rows, &b);
-  *bytes = (int64_t)b;
+  size_t train = 0, fwd = 0;
+  carve_train(nullptr, rows, &train);
+  carve_forward(nullptr, rows, &fwd);
+  *bytes = (int64_t)(train > fwd ? train : fwd);
   return DG_OK;
 }
 
@@ -175,9 +143,9 @@ int dg_mlp_forward(const float *params, const float *X, int64_t rows, float *Y, 
   if (rc != DG_OK) return rc;
   if (rows < 1 || rows >= (int64_t(1) << 26)) return fail(DG_EINVAL, "rows out of range");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  TrainWs t = carve_train(workspace, rows, nullptr);
+  ForwardWs t = carve_forward(workspace, rows, nullptr);
   hipError_t e;
-  if ((e = prep(params, t.w, s)) != hipSuccess) return hip_fail(e, "weight preparation");
+  if ((e = dgsw::launch_prep_weights(params, t.w, s)) != hipSuccess) return hip_fail(e, "weight preparation");
   if ((e = dgsw::launch_mlp_fused(0, nullptr, 0, 0, nullptr, nullptr, X, (int)rows, t.w.W1f, t.w.W2f, t.w.W3t,
                                   params + ob1, params + ob2, t.w.b3p, t.Y, s, nullptr)) != hipSuccess)
     return hip_fail(e, "forward");
@@ -210,47 +178,19 @@ int dg_mlp_train_step(float *params, float *adam_m, float *adam_v, int32_t step,
   TrainWs t = carve_train(workspace, rows, nullptr);
   const int R = (int)rows;
   hipError_t e;
-  if ((e = prep(params, t.w, s)) != hipSuccess) return hip_fail(e, "weight preparation");
-  if ((e = dgsw::launch_to_bf16(X, R, kFeatures, kInPad, t.Xb, s)) != hipSuccess) return hip_fail(e, "features");
-  if ((e = forward(params, t.w, t.Xb, R, t.Z1, t.H1, t.Z2, t.H2, t.Y, s)) != hipSuccess) return hip_fail(e, "forward");
-  // mean squared error over the unmasked outputs
-  int nb = 0;
-  if ((e = dgsw::launch_mse_grad(t.Y, T, bits, R, kOut, kOutPad, scale, t.dY, t.dYf, t.partial, &nb, s)) != hipSuccess)
-    return hip_fail(e, "loss");
-  if (loss && (e = dgsw::launch_sum(t.partial, nb, scale, loss, s)) != hipSuccess) return hip_fail(e, "loss sum");
-  dgsw::GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  // dZ2 = (dY W3^T) * gelu'(Z2)
-  g.A = t.dY; g.B = t.w.W3r; g.M = R; g.N = kHidden; g.K = kOutPad; g.lda = kOutPad; g.ldb = kOutPad;
-  g.Zin = t.Z2; g.Zout = t.dZ2f; g.C = t.dZ2; g.ldc = kHidden;
-  if ((e = dgsw::launch_gemm(true, true, dgsw::kEpiGeluGrad, g, s)) != hipSuccess) return hip_fail(e, "backward 3");
-  // dZ1 = (dZ2 W2^T) * gelu'(Z1)
-  g.A = t.dZ2; g.B = t.w.W2r; g.K = kHidden; g.lda = kHidden; g.ldb = kHidden; g.Zin = t.Z1; g.Zout = t.dZ1f;
-  g.C = t.dZ1;
-  if ((e = dgsw::launch_gemm(true, true, dgsw::kEpiGeluGrad, g, s)) != hipSuccess) return hip_fail(e, "backward 2");
-  // weight gradients: sums over the rows of activation x gradient
-  dgsw::GemmArgs w;
-  std::memset(&w, 0, sizeof(w));
-  w.K = R;
-  w.A = t.H2; w.lda = kHidden; w.M = kHidden; w.B = t.dY; w.ldb = kOutPad; w.N = kOutPad; w.C = t.G3; w.ldc = kOutPad;
-  if ((e = dgsw::launch_gemm_splitk(w, t.split, s)) != hipSuccess) return hip_fail(e, "dW3");
-  w.A = t.H1; w.M = kHidden; w.B = t.dZ2; w.ldb = kHidden; w.N = kHidden; w.C = t.G2; w.ldc = kHidden;
-  if ((e = dgsw::launch_gemm_splitk(w, t.split, s)) != hipSuccess) return hip_fail(e, "dW2");
-  w.A = t.Xb; w.lda = kInPad; w.M = kInPad; w.B = t.dZ1; w.C = t.G1;
-  if ((e = dgsw::launch_gemm_splitk(w, t.split, s)) != hipSuccess) return hip_fail(e, "dW1");
-  float *gr = t.grad;
-  if ((e = dgsw::launch_unpad(t.G1, kFeatures, kHidden, kHidden, gr + oW1, s)) != hipSuccess ||
-      (e = dgsw::launch_colsum(t.dZ1f, R, kHidden, kHidden, t.csum, gr + ob1, s)) != hipSuccess ||
-      (e = dgsw::launch_unpad(t.G2, kHidden, kHidden, kHidden, gr + oW2, s)) != hipSuccess ||
-      (e = dgsw::launch_colsum(t.dZ2f, R, kHidden, kHidden, t.csum, gr + ob2, s)) != hipSuccess ||
-      (e = dgsw::launch_unpad(t.G3, kHidden, kOut, kOutPad, gr + oW3, s)) != hipSuccess ||
-      (e = dgsw::launch_colsum(t.dYf, R, kOut, kOutPad, t.csum, gr + ob3, s)) != hipSuccess)
-    return hip_fail(e, "gradients");
-  if (grads && (e = hipMemcpyAsync(grads, gr, kParams * sizeof(float), hipMemcpyDeviceToDevice, s)) != hipSuccess)
-    return hip_fail(e, "gradient copy");
-  if (lr > 0.f &&
-      (e = dgsw::launch_adam(params, gr, adam_m, adam_v, (int)kParams, lr, 0.9f, 0.999f, 1e-8f, step, s)) != hipSuccess)
-    return hip_fail(e, "Adam");
+  if ((e = dgsw::launch_prep_weights(params, t.w, s)) != hipSuccess) return hip_fail(e, "weight preparation");
+  const int splits = dgsw::train_splits(R), chunks = R / 32;
+  const dgsw::TrainRows tr{params, X,     T,     R,     bits,  scale, t.w,         t.Xf,
+                           t.H1f,  t.H2f, t.DYf, t.D2f, t.D1f, t.bias_part, t.se_part};
+  const dgsw::TrainDw td{t.Xf, t.H1f, t.H2f, t.DYf, t.D2f, t.D1f, chunks, (chunks + splits - 1) / splits, t.part};
+  dgsw::TrainUpdate tu{};
+  tu.part = t.part; tu.bias_part = t.bias_part; tu.se_part = t.se_part;
+  tu.splits = splits; tu.blocks = dgsw::train_row_blocks(R); tu.scale = scale;
+  tu.grads = grads; tu.loss = loss;
+  tu.p = params; tu.m = adam_m; tu.v = adam_v;
+  tu.lr = lr; tu.b1 = 0.9f; tu.b2 = 0.999f; tu.eps = 1e-8f;
+  tu.c1 = 1.f - powf(tu.b1, (float)step); tu.c2 = 1.f - powf(tu.b2, (float)step);
+  if ((e = dgsw::launch_train(tr, td, tu, s)) != hipSuccess) return hip_fail(e, "training step");
   return DG_OK;
 }
 
@@ -348,7 +288,7 @@ int dg_rhs_learned(dg_ctx *ctx, const dg_learned *net, const void *q, void *dqdt
   if (!q || !dqdt) return fail(DG_EINVAL, "NULL argument");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   LearnWs t = carve_learn(workspace, ctx, nullptr);
-  hipError_t e = prep(net->params, t.w, s);
+  hipError_t e = dgsw::launch_prep_weights(net->params, t.w, s);
   if (e != hipSuccess) return hip_fail(e, "weight preparation");
   return learned_stage(ctx, net, t, q, nullptr, dqdt, 0, 0.0, 1.0, 0.0, fallbacks, s);
 }
@@ -361,7 +301,7 @@ int dg_rk_step_learned(dg_ctx *ctx, const dg_learned *net, void *q, void *work, 
   if (nsteps < 0 || !std::isfinite(dt)) return fail(DG_EINVAL, "bad nsteps or dt");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   LearnWs t = carve_learn(workspace, ctx, nullptr);
-  hipError_t e = prep(net->params, t.w, s);
+  hipError_t e = dgsw::launch_prep_weights(net->params, t.w, s);
   if (e != hipSuccess) return hip_fail(e, "weight preparation");
   const size_t bytes = ctx->state_n * ctx->elem_bytes;
   char *w0 = static_cast<char *>(work);

@@ -49,168 +49,12 @@ __device__ __forceinline__ float gelu_f(float z) {
   const float az = fabsf(z);
   return fmaf(-az * gelu_as::half_poly(az), gelu_as::gauss(z), fmaxf(z, 0.0f));
 }
-__device__ __forceinline__ float gelu_grad_f(float z) {
-  const float hp = gelu_as::half_poly(fabsf(z));
-  return fmaf(gelu_as::gauss(z), fmaf(z, 0.39894228040143268f, -copysignf(hp, z)), z >= 0.0f ? 1.0f : 0.0f);
-}
-
-// ------------------------------------------------------------------ GEMM
-// C[M][N] = A(m, k) B(k, n) over k < K (K % 32 == 0, N % 32 == 0), with
-//   A_KC: A(m, k) = A[m * lda + k]   (else A[k * lda + m])
-//   B_KC: B(k, n) = B[n * ldb + k]   (else B[k * ldb + n])
-// A workgroup of 4 wavefronts computes a 64 x 64 tile, a wavefront 32 x 32
-// (2 x 2 MFMA tiles); rows >= M are read clamped and not written.
-template <bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(const __bf16 *__restrict__ A, const __bf16 *__restrict__ B,
-                                              int M, int N, int K, int lda, int ldb,
-                                              const float *__restrict__ bias,
-                                              const float *__restrict__ Zin, float *__restrict__ Zout,
-                                              void *__restrict__ C, int ldc) {
-  const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m0 = blockIdx.x * 64 + (wv >> 1) * 32;
-  const int n0 = blockIdx.y * 64 + (wv & 1) * 32;
-  if (n0 >= N) return;
-  // split K: workgroup z sums k in [z kc, min(K, (z + 1) kc)) into the z-th
-  // partial product C + z M ldc (gridDim.z == 1: the whole K into C)
-  const int kc = gridDim.z == 1 ? K : ((K / 32 + gridDim.z - 1) / gridDim.z) * 32;
-  const int kb = blockIdx.z * kc, ke = kb + kc < K ? kb + kc : K;
-  if (gridDim.z > 1) C = static_cast<float *>(C) + (size_t)blockIdx.z * M * ldc;
-  const int r = lane & 15, kq = (lane >> 4) * 8;
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  int ma[2], nb[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = m0 + 16 * i + r;
-    ma[i] = m < M ? m : M - 1;
-    nb[i] = n0 + 16 * i + r;
-  }
-  for (int k0 = kb; k0 < ke; k0 += 32) {
-    bf16x8 a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if constexpr (A_KC) {
-        a[i] = *reinterpret_cast<const bf16x8 *>(A + (size_t)ma[i] * lda + k0 + kq);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[i][j] = A[(size_t)(k0 + kq + j) * lda + ma[i]];
-      }
-      if constexpr (B_KC) {
-        b[i] = *reinterpret_cast<const bf16x8 *>(B + (size_t)nb[i] * ldb + k0 + kq);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) b[i][j] = B[(size_t)(k0 + kq + j) * ldb + nb[i]];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-  }
-  // epilogue: lane holds rows 4(l/16)+e of each 16 x 16 tile, column l%16
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int m = m0 + 16 * i + (lane >> 4) * 4 + e;
-        const int n = n0 + 16 * j + r;
-        if (m >= M) continue;
-        float z = acc[i][j][e];
-        const size_t o = (size_t)m * ldc + n;
-        if constexpr (EPI == kEpiBiasGelu) {
-          z += bias[n];
-          if (Zout) Zout[o] = z;
-          static_cast<__bf16 *>(C)[o] = (__bf16)gelu_f(z);
-        } else if constexpr (EPI == kEpiBias) {
-          static_cast<float *>(C)[o] = z + bias[n];
-        } else if constexpr (EPI == kEpiGeluGrad) {
-          z *= gelu_grad_f(Zin[o]);
-          if (Zout) Zout[o] = z;
-          static_cast<__bf16 *>(C)[o] = (__bf16)z;
-        } else {
-          static_cast<float *>(C)[o] = z;
-        }
-      }
-}
-
-template <bool A_KC, bool B_KC, int EPI>
-static hipError_t gemm_t(const GemmArgs &g, hipStream_t s) {
-  dim3 grid((g.M + 63) / 64, (g.N + 63) / 64);
-  hipLaunchKernelGGL((k_gemm<A_KC, B_KC, EPI>), grid, dim3(256), 0, s, g.A, g.B, g.M, g.N, g.K, g.lda,
-                     g.ldb, g.bias, g.Zin, g.Zout, g.C, g.ldc);
-  return hipGetLastError();
-}
-
-// Sum of nsplit partial products part[z][n] over z in order (deterministic):
-// four consecutive outputs per thread, the loads of several z in flight.
-__global__ void k_sum_split(const float *__restrict__ part, int nsplit, int n4, float *__restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n4) return;
-  const float4 *p = reinterpret_cast<const float4 *>(part) + i;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-  for (int z = 0; z < nsplit; ++z) {
-    const float4 v = p[(size_t)z * n4];
-    acc.x += v.x;
-    acc.y += v.y;
-    acc.z += v.z;
-    acc.w += v.w;
-  }
-  reinterpret_cast<float4 *>(out)[i] = acc;
-}
-// the same one output per thread (n not a multiple of 4, or unaligned)
-__global__ void k_sum_split1(const float *__restrict__ part, int nsplit, int n, float *__restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float acc = 0.f;
-  for (int z = 0; z < nsplit; ++z) acc += part[(size_t)z * n + i];
-  out[i] = acc;
-}
-
-hipError_t launch_sum_split(const float *part, int nsplit, int n, float *out, hipStream_t s) {
-  if (n % 4 == 0 && reinterpret_cast<uintptr_t>(part) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0)
-    hipLaunchKernelGGL(k_sum_split, dim3((n / 4 + 255) / 256), dim3(256), 0, s, part, nsplit, n / 4, out);
-  else
-    hipLaunchKernelGGL(k_sum_split1, dim3((n + 255) / 256), dim3(256), 0, s, part, nsplit, n, out);
-  return hipGetLastError();
-}
-
-int gemm_splits(int K) {
-  const int s = (K + 255) / 256;
-  return s < 1 ? 1 : (s > kMaxSplits ? kMaxSplits : s);
-}
-
-hipError_t launch_gemm_splitk(const GemmArgs &g, float *partial, hipStream_t s) {
-  if (g.M <= 0) return hipSuccess;
-  if (g.K % 32 || g.N % 32) return hipErrorInvalidValue;
-  const int z = gemm_splits(g.K);
-  GemmArgs p = g;
-  p.C = partial;
-  dim3 grid((g.M + 63) / 64, (g.N + 63) / 64, z);
-  hipLaunchKernelGGL((k_gemm<false, false, kEpiPlain>), grid, dim3(256), 0, s, p.A, p.B, p.M, p.N, p.K, p.lda,
-                     p.ldb, p.bias, p.Zin, p.Zout, p.C, p.ldc);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_sum_split(partial, z, g.M * g.ldc, static_cast<float *>(g.C), s);
-}
-
-hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, const GemmArgs &g, hipStream_t s) {
-  if (g.M <= 0) return hipSuccess;
-  if (g.K % 32 || g.N % 32) return hipErrorInvalidValue;
-#define DGSW_GEMM(AK, BK, E) \
-  if (a_kc == AK && b_kc == BK && epi == E) return gemm_t<AK, BK, E>(g, s);
-  DGSW_GEMM(true, true, kEpiBiasGelu) DGSW_GEMM(true, true, kEpiBias)
-  DGSW_GEMM(true, true, kEpiGeluGrad) DGSW_GEMM(true, true, kEpiPlain)
-  DGSW_GEMM(false, false, kEpiPlain)
-#undef DGSW_GEMM
-  return hipErrorInvalidValue;
+// GELU(z) and, in place of z, GELU'(z): one reciprocal and one exponential for both.
+__device__ __forceinline__ float gelu_and_grad(float &z) {
+  const float az = fabsf(z), hp = gelu_as::half_poly(az), e = gelu_as::gauss(z);
+  const float h = fmaf(-az * hp, e, fmaxf(z, 0.0f));
+  z = fmaf(e, fmaf(z, 0.39894228040143268f, -copysignf(hp, z)), z >= 0.0f ? 1.0f : 0.0f);
+  return h;
 }
 
 // ------------------------------------------------------------------ fused inference
@@ -559,157 +403,476 @@ hipError_t launch_mlp_fused(int dtype, const void *q, int n_lon, int n_lat, cons
 }
 
 // ------------------------------------------------------------------ weights
-// FP32 parameter vector -> BF16 operand copies: Wt[n][kp] (forward, k
-// contiguous, k padded with zeros to kp) and Wr[k][np] (backward, rows padded
-// to the next layer's padded width np, columns beyond n zero), and Wf, the
-// forward weights in the order the fused kernel's wavefronts read them: for
-// units [16 u, 16 u + 16) and inputs [32 c, 32 c + 32) one 1 KB block,
-// ((u K/32 + c) 64 + lane) 8 + j holding unit 16 u + lane % 16 and input
-// 32 c + 8 (lane / 16) + j (the MFMA A-operand layout), so that each of its
-// loads is one contiguous kilobyte (kp % 32 == 0, np % 16 == 0).
-__global__ void k_prep_weights(const float *__restrict__ W, int k_in, int n_out, int kp, int np_,
-                               __bf16 *__restrict__ Wt, __bf16 *__restrict__ Wr, __bf16 *__restrict__ Wf) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int total = kp * np_;
-  if (idx >= total) return;
-  const int k = idx / np_, n = idx - k * np_;
-  const float w = (k < k_in && n < n_out) ? W[(size_t)k * n_out + n] : 0.0f;
-  if (Wr) Wr[(size_t)k * np_ + n] = (__bf16)w;
-  if (Wt) Wt[(size_t)n * kp + k] = (__bf16)w;
-  if (Wf) {
-    const int lane = n % 16 + 16 * ((k % 32) / 8);
-    Wf[((size_t)(n / 16) * (kp / 32) + k / 32) * 512 + lane * 8 + k % 8] = (__bf16)w;
-  }
+// FP32 parameter vector -> BF16 operand copies, one launch for all of them
+// (a launch costs more than any of the copies).  Fragment order of a matrix
+// whose rows are MFMA A-operand rows and whose columns k are contracted: for
+// rows [16 u, 16 u + 16) and columns [32 c, 32 c + 32) one 1 KB block,
+// ((u K/32 + c) 64 + lane) 8 + j holding row 16 u + lane % 16 and column
+// 32 c + 8 (lane / 16) + j, so that each load of a wavefront is one contiguous
+// kilobyte.  Padded entries are zero.
+__device__ __forceinline__ int frag_at(int row, int k, int K) {
+  return ((row / 16) * (K / 32) + k / 32) * 512 + (row % 16 + 16 * ((k % 32) / 8)) * 8 + k % 8;
 }
 
-hipError_t launch_prep_weights(const float *W, int k_in, int n_out, int kp, int np_, __bf16 *Wt, __bf16 *Wr,
-                               __bf16 *Wf, hipStream_t s) {
-  if (Wf && (kp % 32 || np_ % 16)) return hipErrorInvalidValue;
-  const int total = kp * np_;
-  hipLaunchKernelGGL(k_prep_weights, dim3((total + 255) / 256), dim3(256), 0, s, W, k_in, n_out, kp, np_, Wt, Wr,
-                     Wf);
+__global__ __launch_bounds__(256) void k_prep_weights(const float *__restrict__ P, PrepWeights w) {
+  constexpr int n1 = kInPad * kHidden, n2 = kHidden * kHidden, n3 = kHidden * kOutPad;
+  int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n1) {
+    const int k = i / kHidden, n = i % kHidden;
+    w.W1f[frag_at(n, k, kInPad)] = (__bf16)(k < kFeatures ? P[oW1 + (size_t)k * kHidden + n] : 0.0f);
+    return;
+  }
+  i -= n1;
+  if (i < n2) {
+    const int k = i / kHidden, n = i % kHidden;
+    const __bf16 v = (__bf16)P[oW2 + i];
+    w.W2f[frag_at(n, k, kHidden)] = v;
+    if (w.W2rf) w.W2rf[frag_at(k, n, kHidden)] = v;
+    return;
+  }
+  i -= n2;
+  if (i < n3) {
+    const int k = i / kOutPad, n = i % kOutPad;
+    const __bf16 v = (__bf16)(n < kOut ? P[oW3 + (size_t)k * kOut + n] : 0.0f);
+    if (w.W3t) w.W3t[(size_t)n * kHidden + k] = v;
+    if (w.W3f) w.W3f[frag_at(n, k, kHidden)] = v;
+    if (w.W3rf) w.W3rf[frag_at(k, n, kOutPad)] = v;
+    return;
+  }
+  i -= n3;
+  if (i < kOutPad) w.b3p[i] = i < kOut ? P[ob3 + i] : 0.0f;
+}
+
+hipError_t launch_prep_weights(const float *P, const PrepWeights &w, hipStream_t s) {
+  constexpr int total = kInPad * kHidden + kHidden * kHidden + kHidden * kOutPad + kOutPad;
+  hipLaunchKernelGGL(k_prep_weights, dim3((total + 255) / 256), dim3(256), 0, s, P, w);
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ loss
-// dY = 2 (Y - T) mask / (rows * sum(mask)) as BF16 (padded columns zero) and
-// the squared error summed per block into partial[blockIdx.x].  The 0/1 mask
-// of the outputs arrives as bits (bit n: output n counts).
-__global__ __launch_bounds__(256) void k_mse_grad(const float *__restrict__ Y, const float *__restrict__ T,
-                                                  unsigned mask_bits, int rows, int n_out, int ld,
-                                                  float scale, __bf16 *__restrict__ dY, float *__restrict__ dYf,
-                                                  float *__restrict__ partial) {
-  __shared__ float sh[256];
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  float se = 0.f;
-  if (idx < rows * ld) {
-    const int m = idx / ld, n = idx - m * ld;
-    float g = 0.f;
-    if (n < n_out && ((mask_bits >> n) & 1u)) {
-      const float d = Y[(size_t)m * ld + n] - T[(size_t)m * n_out + n];
-      se = d * d;
-      g = 2.f * d * scale;
-    }
-    dY[idx] = (__bf16)g;
-    dYf[idx] = g;
+// ------------------------------------------------------------------ training step
+// One training step is three kernels after the weights' preparation:
+//   k_train_rows    everything that is local to a row: both passes through the
+//                   network for 32 rows per workgroup, activations in LDS,
+//                   pre-activations in registers (the backward pass needs each
+//                   in the lane that formed it); leaves the factors of the
+//                   weight gradients in fragment order and the workgroup's
+//                   sums of the bias gradients and of the squared error;
+//   k_train_dw      the weight gradients, sums over the rows of activation x
+//                   gradient, split over ranges of rows;
+//   k_train_update  the ranges' sums in order, and Adam.
+// The 29 launches this replaces (one GEMM, conversion, column sum or copy
+// each) took 157 us at 8192 rows, launches and memory round trips almost all of
+// it; these take 37 (rows 21.8, one tile per CU: a serial chain of five products
+// and their barriers; gradients 8.7, update 5.2, weights 3).  Rounding points as before: BF16 factors of every product, FP32
+// accumulation, bias, GELU, loss and gradients in FP32.
+constexpr int kTrRows = 32;               // rows of a tile: one K block of the weight gradients
+constexpr int kLdX = kInPad + 8, kLdY = kOutPad + 8;   // LDS row strides in BF16
+
+// acc[nt][mt] of this wavefront's units [32 wv, +32) = W in^T over K inputs, A
+// fragments w, rows of `in` (stride ld) as B.
+template <int K>
+__device__ __forceinline__ void train_product(const bf16x8 (&w)[K / 32][2], const __bf16 *in, int ld, int lane,
+                                              f32x4 (&acc)[2][2]) {
+  const int r = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) acc[nt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < K / 32; ++ks) {
+    bf16x8 b[2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) b[mt] = *reinterpret_cast<const bf16x8 *>(in + (16 * mt + r) * ld + 32 * ks + kq);
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+        acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], b[mt], acc[nt][mt], 0, 0, 0);
   }
-  sh[threadIdx.x] = se;
+}
+
+template <int K>
+__device__ __forceinline__ void train_weights(const __bf16 *__restrict__ Wf, int wv, int lane, bf16x8 (&w)[K / 32][2]) {
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+    for (int ks = 0; ks < K / 32; ++ks)
+      w[ks][nt] = *reinterpret_cast<const bf16x8 *>(Wf + ((size_t)(2 * wv + nt) * (K / 32) + ks) * 512 + lane * 8);
+}
+
+// out = BF16(gelu(z + bias)) into LDS rows of stride kLd; z becomes gelu'.
+__device__ __forceinline__ void train_gelu(f32x4 (&z)[2][2], const float *__restrict__ bias, __bf16 *out, int wv,
+                                           int lane) {
+  const int r = lane & 15;
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int n0 = 32 * wv + 16 * nt + (lane >> 4) * 4;
+    const float b[4] = {bias[n0], bias[n0 + 1], bias[n0 + 2], bias[n0 + 3]};
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      bf16x4 h;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float zi = z[nt][mt][i] + b[i];
+        h[i] = (__bf16)gelu_and_grad(zi);
+        z[nt][mt][i] = zi;
+      }
+      *reinterpret_cast<bf16x4 *>(out + (16 * mt + r) * kLd + n0) = h;
+    }
+  }
+}
+
+// d = acc gelu' as BF16 into LDS; its sum over the tile's rows added to db
+// (lanes of one 16-lane group hold the rows of a unit; lane % 16 == 0 the sum).
+__device__ __forceinline__ void train_gelu_grad(const f32x4 (&acc)[2][2], const f32x4 (&gp)[2][2], __bf16 *out, int wv,
+                                                int lane, float (&db)[2][4]) {
+  const int r = lane & 15;
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int n0 = 32 * wv + 16 * nt + (lane >> 4) * 4;
+    float d[2][4];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      bf16x4 h;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        d[mt][i] = acc[nt][mt][i] * gp[nt][mt][i];
+        h[i] = (__bf16)d[mt][i];
+      }
+      *reinterpret_cast<bf16x4 *>(out + (16 * mt + r) * kLd + n0) = h;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float t = d[0][i] + d[1][i];
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+      db[nt][i] += t;
+    }
+  }
+}
+
+// A tile's factor in[32 rows][units] to fragment order (the rows contracted):
+// block u of the tile, 16 units, is one contiguous kilobyte.
+__device__ __forceinline__ void train_fragments(const __bf16 *in, int ld, int units, __bf16 *__restrict__ out, int wv,
+                                                int lane) {
+  const int r = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll 1
+  for (int u = wv; u < units / 16; u += kWaves) {
+    bf16x8 f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f[j] = in[(kq + j) * ld + 16 * u + r];
+    *reinterpret_cast<bf16x8 *>(out + (size_t)u * 512 + lane * 8) = f;
+  }
+}
+
+__global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * kWaves) void k_train_rows(TrainRows a) {
+  __shared__ __attribute__((aligned(16))) __bf16 sx[kTrRows * kLdX];
+  __shared__ __attribute__((aligned(16))) __bf16 sh1[kTrRows * kLd], sh2[kTrRows * kLd];
+  __shared__ __attribute__((aligned(16))) __bf16 sd1[kTrRows * kLd], sd2[kTrRows * kLd];
+  __shared__ __attribute__((aligned(16))) __bf16 sdy[kTrRows * kLdY];
+  __shared__ float sse[kWaves];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float db1[2][4], db2[2][4], db3[4], se = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    db1[0][i] = db1[1][i] = db2[0][i] = db2[1][i] = 0.f;
+    db3[i] = 0.f;
+  }
+  const int tiles = a.rows / kTrRows;
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    // unknown to the compiler in every round, or it computes all of a round's
+    // addresses before the loop and spills them
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, r = lane & 15;
+    const size_t row0 = (size_t)tile * kTrRows;
+    bf16x8 w1[kInPad / 32][2], w2[kHidden / 32][2];
+    // inputs (any alignment of X), then the forward weights: loads complete in order
+    float xv[(kTrRows * kFeatures + 64 * kWaves - 1) / (64 * kWaves)];
+#pragma unroll
+    for (int n = 0; n < (int)(sizeof(xv) / sizeof(float)); ++n) {
+      const int idx = tid + 64 * kWaves * n;
+      xv[n] = idx < kTrRows * kFeatures ? a.X[row0 * kFeatures + idx] : 0.f;
+    }
+    train_weights<kInPad>(a.w.W1f, wv, lane, w1);
+    train_weights<kHidden>(a.w.W2f, wv, lane, w2);
+#pragma unroll
+    for (int n = 0; n < (int)(sizeof(xv) / sizeof(float)); ++n) {
+      const int idx = tid + 64 * kWaves * n;
+      if (idx < kTrRows * kFeatures) sx[(idx / kFeatures) * kLdX + idx % kFeatures] = (__bf16)xv[n];
+    }
+    for (int idx = tid; idx < kTrRows * (kInPad - kFeatures); idx += 64 * kWaves)
+      sx[(idx / (kInPad - kFeatures)) * kLdX + kFeatures + idx % (kInPad - kFeatures)] = (__bf16)0.f;
+    __syncthreads();
+    f32x4 z1[2][2], z2[2][2], acc[2][2];
+    train_product<kInPad>(w1, sx, kLdX, lane, z1);
+    train_gelu(z1, a.P + ob1, sh1, wv, lane);
+    __syncthreads();
+    train_product<kHidden>(w2, sh1, kLd, lane, z2);
+    // output layer, loss and its gradient: wavefront 2 mt + nt < 4 takes 16
+    // rows x 16 outputs; the weights it and the way back need are requested
+    // ahead of their barriers
+    const int mt = (wv >> 1) & 1, nt = wv & 1, kq = (lane >> 4) * 8, n0 = 16 * nt + (lane >> 4) * 4;
+    bf16x8 w3r[1][2], w3[kHidden / 32];
+    float tv[4], b3[4];
+#pragma unroll
+    for (int ks = 0; ks < kHidden / 32; ++ks)
+      w3[ks] = *reinterpret_cast<const bf16x8 *>(a.w.W3f + ((size_t)nt * (kHidden / 32) + ks) * 512 + lane * 8);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      tv[i] = n0 + i < kOut ? a.T[(row0 + 16 * mt + r) * kOut + n0 + i] : 0.f;
+      b3[i] = a.w.b3p[n0 + i];
+    }
+    train_weights<kOutPad>(a.w.W3rf, wv, lane, w3r);
+    train_gelu(z2, a.P + ob2, sh2, wv, lane);
+    __syncthreads();
+    train_weights<kHidden>(a.w.W2rf, wv, lane, w2);
+    if (wv < 4) {
+      f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < kHidden / 32; ++ks) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8 *>(sh2 + (16 * mt + r) * kLd + 32 * ks + kq);
+        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3[ks], b, y, 0, 0, 0);
+      }
+      bf16x4 h;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float g = 0.f;
+        if (n0 + i < kOut && ((a.mask_bits >> (n0 + i)) & 1u)) {
+          const float d = (y[i] + b3[i]) - tv[i];
+          se += d * d;
+          g = 2.f * d * a.scale;
+        }
+        h[i] = (__bf16)g;
+        float t = g;
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+        db3[i] += t;
+      }
+      *reinterpret_cast<bf16x4 *>(sdy + (16 * mt + r) * kLdY + n0) = h;
+    }
+    __syncthreads();
+    train_product<kOutPad>(w3r, sdy, kLdY, lane, acc);
+    train_gelu_grad(acc, z2, sd2, wv, lane, db2);
+    __syncthreads();
+    train_product<kHidden>(w2, sd2, kLd, lane, acc);
+    train_gelu_grad(acc, z1, sd1, wv, lane, db1);
+    train_fragments(sx, kLdX, kInPad, a.Xf + row0 * kInPad, wv, lane);
+    train_fragments(sh1, kLd, kHidden, a.H1f + row0 * kHidden, wv, lane);
+    train_fragments(sh2, kLd, kHidden, a.H2f + row0 * kHidden, wv, lane);
+    train_fragments(sd2, kLd, kHidden, a.D2f + row0 * kHidden, wv, lane);
+    train_fragments(sdy, kLdY, kOutPad, a.DYf + row0 * kOutPad, wv, lane);
+    __syncthreads();
+    train_fragments(sd1, kLd, kHidden, a.D1f + row0 * kHidden, wv, lane);
+    __syncthreads();          // the next tile overwrites the LDS arrays
+  }
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15;
+  // this workgroup's sums: [b1 | b2 | b3 of rows 0..15 | .. of rows 16..31], squared error
+  float *bp = a.bias_part + (size_t)blockIdx.x * kBiasPart;
+  if (r == 0) {
+    const int n0 = 32 * wv + (lane >> 4) * 4;
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bp[n0 + 16 * nt + i] = db1[nt][i];
+        bp[kHidden + n0 + 16 * nt + i] = db2[nt][i];
+      }
+    if (wv < 4)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        bp[2 * kHidden + kOutPad * (wv >> 1) + 16 * (wv & 1) + (lane >> 4) * 4 + i] = db3[i];
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) se += __shfl_xor(se, off, 64);
+  if (lane == 0) sse[wv] = se;
+  __syncthreads();
+  if (tid == 0) a.se_part[blockIdx.x] = (sse[0] + sse[1]) + (sse[2] + sse[3]);
+}
+
+int train_row_blocks(int rows) {
+  const int t = rows / kTrRows;
+  return t < kMaxTrainBlocks ? t : kMaxTrainBlocks;
+}
+
+// Weight gradients: a workgroup takes 64 x 64 outputs (64 x 32 of the output
+// layer's) of one matrix over one range of rows; its eight wavefronts take
+// every eighth block of 32 rows (eight fragments of a kilobyte, sixteen MFMAs
+// each) and their sums meet in LDS.  28 workgroups a range: 16 of W2, 8 of W1,
+// 4 of W3.  The fragments come from other XCDs' caches, so latency bounds it:
+// a wavefront has two blocks at 8192 rows, all its loads in flight at once, and
+// a range belongs to one XCD (8.7 us at 8192 rows; 11.0 with the ranges spread
+// over all XCDs, 10.2 with one wavefront per output tile and 256 rows).
+constexpr int kDwWaves = 8, kDwJobs = 28;
+
+template <int NT>
+__device__ __forceinline__ void train_dw(const __bf16 *__restrict__ A, int ua, const __bf16 *__restrict__ B, int ub,
+                                         int c0, int c1, int wv, int lane, f32x4 *sh, float *__restrict__ C, int ldc) {
+  f32x4 acc[4][NT];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int c = c0 + wv; c < c1; c += kDwWaves) {
+    bf16x8 a[4], b[NT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(A + ((size_t)c * ua + i) * 512 + lane * 8);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) b[j] = *reinterpret_cast<const bf16x8 *>(B + ((size_t)c * ub + j) * 512 + lane * 8);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+  }
+  // wavefronts 4 .. 7 to LDS, added by 0 .. 3; those four again, and
+  // wavefront w adds the tiles (i, j) of row i = w
+  f32x4 *mine = sh + (wv & 3) * (4 * NT * 64) + lane;
+  if (wv >= 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) mine[(i * NT + j) * 64] = acc[i][j];
+  }
+  __syncthreads();
+  if (wv < 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) mine[(i * NT + j) * 64] += acc[i][j];
+  }
+  __syncthreads();
+  if (wv < 4) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const f32x4 *t = sh + (wv * NT + j) * 64 + lane;
+      const f32x4 v = (t[0] + t[4 * NT * 64]) + (t[8 * NT * 64] + t[12 * NT * 64]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) C[(size_t)(16 * wv + (lane >> 4) * 4 + e) * ldc + 16 * j + (lane & 15)] = v[e];
+    }
+  }
+}
+
+__global__ __launch_bounds__(64 * kDwWaves) void k_train_dw(TrainDw a) {
+  __shared__ f32x4 sh[4 * 16 * 64];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // workgroups are dispatched round-robin over the 8 XCDs: each takes a
+  // contiguous run of (range, job), so a range's rows are read by one XCD
+  const int nb = gridDim.x, x = blockIdx.x & 7, nx = nb >> 3, rem = nb & 7;
+  const int id = x * nx + (x < rem ? x : rem) + (blockIdx.x >> 3);
+  const int range = id / kDwJobs, job = id - range * kDwJobs;
+  const int c0 = range * a.per, c1 = c0 + a.per < a.chunks ? c0 + a.per : a.chunks;
+  float *G = a.part + (size_t)range * kGradPart;
+  constexpr int UH = kHidden / 16, UX = kInPad / 16, UY = kOutPad / 16;
+  if (job < 16) {
+    const int m = job >> 2, n = job & 3;
+    train_dw<4>(a.H1f + m * 4 * 512, UH, a.D2f + n * 4 * 512, UH, c0, c1, wv, lane, sh,
+                G + oG2 + (size_t)m * 64 * kHidden + n * 64, kHidden);
+  } else if (job < 24) {
+    const int m = (job - 16) >> 2, n = job & 3;
+    train_dw<4>(a.Xf + m * 4 * 512, UX, a.D1f + n * 4 * 512, UH, c0, c1, wv, lane, sh,
+                G + oG1 + (size_t)m * 64 * kHidden + n * 64, kHidden);
+  } else {
+    const int m = job - 24;
+    train_dw<2>(a.H2f + m * 4 * 512, UH, a.DYf, UY, c0, c1, wv, lane, sh, G + oG3 + (size_t)m * 64 * kOutPad, kOutPad);
+  }
+}
+
+int train_splits(int rows) {
+  const int s = (rows + 511) / 512;
+  return s < 1 ? 1 : (s > kMaxSplits ? kMaxSplits : s);
+}
+
+// Gradients and Adam, a thread per weight (the ranges' sums added in order);
+// the biases by 32 threads each over the workgroups' sums, in blocks of their
+// own; the last block the loss.
+__device__ __forceinline__ void train_param(const TrainUpdate &a, int i, float g) {
+  if (a.grads) a.grads[i] = g;
+  if (a.lr > 0.f) {
+    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * g;
+    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * g * g;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    a.p[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+  }
+}
+
+constexpr int kUpW1 = kFeatures * kHidden / 256, kUpW2 = kHidden * kHidden / 256, kUpW3 = kHidden * kOut / 256;
+constexpr int kUpB = (2 * kHidden + kOutPad) / 8;       // 8 biases per block, 32 threads each
+
+__global__ __launch_bounds__(256) void k_train_update(TrainUpdate a) {
+  __shared__ float sh[256];
+  const int t = threadIdx.x;
+  int b = blockIdx.x;
+  if (b < kUpW1 + kUpW2 + kUpW3) {
+    int i, o;                                           // parameter, place in a range's sums
+    if (b < kUpW1) {
+      const int n = b * 256 + t;
+      i = (int)oW1 + n;
+      o = oG1 + n;
+    } else if (b < kUpW1 + kUpW2) {
+      const int n = (b - kUpW1) * 256 + t;
+      i = (int)oW2 + n;
+      o = oG2 + n;
+    } else {
+      const int n = (b - kUpW1 - kUpW2) * 256 + t;
+      i = (int)oW3 + n;
+      o = oG3 + n / kOut * kOutPad + n % kOut;
+    }
+    const float *p = a.part + o;
+    float g = 0.f;
+#pragma unroll 16
+    for (int z = 0; z < a.splits; ++z) g += p[(size_t)z * kGradPart];
+    train_param(a, i, g);
+    return;
+  }
+  b -= kUpW1 + kUpW2 + kUpW3;
+  if (b < kUpB) {
+    const int j = b * 8 + (t & 7);                      // of b1, b2, b3 (padded)
+    float g = 0.f;
+#pragma unroll 8
+    for (int k = t >> 3; k < a.blocks; k += 32) {
+      const float *p = a.bias_part + (size_t)k * kBiasPart + j;
+      g += j < 2 * kHidden ? p[0] : p[0] + p[kOutPad];
+    }
+    sh[t] = g;
+    __syncthreads();
+    for (int off = 128; off >= 8; off >>= 1) {
+      if (t < off) sh[t] += sh[t + off];
+      __syncthreads();
+    }
+    if (t >= 8) return;
+    if (j < kHidden) train_param(a, (int)ob1 + j, sh[t]);
+    else if (j < 2 * kHidden) train_param(a, (int)ob2 + j - kHidden, sh[t]);
+    else if (j < 2 * kHidden + kOut) train_param(a, (int)ob3 + j - 2 * kHidden, sh[t]);
+    return;
+  }
+  float se = 0.f;
+  for (int k = t; k < a.blocks; k += 256) se += a.se_part[k];
+  sh[t] = se;
   __syncthreads();
   for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
+    if (t < off) sh[t] += sh[t + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[blockIdx.x] = sh[0];
+  if (t == 0) *a.loss = a.scale * sh[0];
 }
 
-hipError_t launch_mse_grad(const float *Y, const float *T, unsigned mask_bits, int rows, int n_out, int ld,
-                           float scale, __bf16 *dY, float *dYf, float *partial, int *nblocks, hipStream_t s) {
-  *nblocks = (rows * ld + 255) / 256;
-  hipLaunchKernelGGL(k_mse_grad, dim3(*nblocks), dim3(256), 0, s, Y, T, mask_bits, rows, n_out, ld, scale, dY, dYf,
-                     partial);
-  return hipGetLastError();
-}
-
-// Column sums of G[rows][ld] for the first n columns (bias gradients) in two
-// deterministic passes: workgroup (column block, chunk) sums its chunk of
-// rows for 64 columns (4 row lanes per column, then a fixed tree), and
-// launch_sum_split adds the chunks in order.
-__global__ __launch_bounds__(256) void k_colsum_part(const float *__restrict__ G, int rows, int n, int ld,
-                                                     int chunk, float *__restrict__ part) {
-  __shared__ float sh[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), rl = threadIdx.x >> 6;
-  const int r0 = blockIdx.y * chunk, r1 = r0 + chunk < rows ? r0 + chunk : rows;
-  float acc = 0.f;
-  if (c < n)
-    for (int m = r0 + rl; m < r1; m += 4) acc += G[(size_t)m * ld + c];
-  sh[rl][threadIdx.x & 63] = acc;
-  __syncthreads();
-  if (rl == 0 && c < n)
-    part[(size_t)blockIdx.y * n + c] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
-}
-
-int colsum_chunks(int rows) {
-  const int c = (rows + 63) / 64;
-  return c < 1 ? 1 : (c > kMaxColChunks ? kMaxColChunks : c);
-}
-
-hipError_t launch_colsum(const float *G, int rows, int n, int ld, float *part, float *out, hipStream_t s) {
-  const int chunks = colsum_chunks(rows);
-  const int chunk = (rows + chunks - 1) / chunks;
-  hipLaunchKernelGGL(k_colsum_part, dim3((n + 63) / 64, chunks), dim3(256), 0, s, G, rows, n, ld, chunk, part);
+hipError_t launch_train(const TrainRows &r, const TrainDw &d, const TrainUpdate &u, hipStream_t s) {
+  static_assert(kUpW1 * 256 == kFeatures * kHidden && kUpW2 * 256 == kHidden * kHidden && kUpW3 * 256 == kHidden * kOut &&
+                    kUpB * 8 == 2 * kHidden + kOutPad,
+                "update blocks");
+  hipLaunchKernelGGL(k_train_rows, dim3(u.blocks), dim3(64 * kWaves), 0, s, r);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_sum_split(part, chunks, n, out, s);
-}
-
-// scale * (sum of `n` partials), single block, fixed order, into *out.
-__global__ __launch_bounds__(256) void k_sum(const float *__restrict__ p, int n, float scale,
-                                             float *__restrict__ out) {
-  __shared__ float sh[256];
-  float acc = 0.f;
-  for (int k = threadIdx.x; k < n; k += 256) acc += p[k];
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = scale * sh[0];
-}
-
-hipError_t launch_sum(const float *p, int n, float scale, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, p, n, scale, out);
+  hipLaunchKernelGGL(k_train_dw, dim3(kDwJobs * u.splits), dim3(64 * kDwWaves), 0, s, d);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_train_update, dim3(kUpW1 + kUpW2 + kUpW3 + kUpB + (u.loss ? 1 : 0)), dim3(256), 0, s, u);
   return hipGetLastError();
 }
 
-// X[rows][n] (FP32) -> Xb[rows][ldx] (BF16, columns >= n zero)
-__global__ void k_to_bf16(const float *__restrict__ X, int rows, int n, int ldx, __bf16 *__restrict__ Xb) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)rows * ldx) return;
-  const size_t m = idx / ldx;
-  const int k = (int)(idx - m * ldx);
-  Xb[idx] = (__bf16)(k < n ? X[m * n + k] : 0.0f);
-}
-
-hipError_t launch_to_bf16(const float *X, int rows, int n, int ldx, __bf16 *Xb, hipStream_t s) {
-  const size_t total = (size_t)rows * ldx;
-  hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, X, rows, n, ldx, Xb);
-  return hipGetLastError();
-}
-
-// b[n] -> out[np_] with zeros beyond n
-__global__ void k_pad(const float *__restrict__ b, int n, int np_, float *__restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < np_) out[i] = i < n ? b[i] : 0.0f;
-}
-
-hipError_t launch_pad(const float *b, int n, int np_, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_pad, dim3((np_ + 63) / 64), dim3(64), 0, s, b, n, np_, out);
-  return hipGetLastError();
-}
-
-// Gradient of a weight matrix W[k_in][n_out] from the padded GEMM result
-// G[kp][np_] (rows/cols beyond the real sizes dropped) into the flat vector.
+// The real columns of a padded matrix G[k_in][np_] into out[k_in][n_out].
 __global__ void k_unpad(const float *__restrict__ G, int k_in, int n_out, int np_, float *__restrict__ out) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= k_in * n_out) return;
@@ -720,27 +883,6 @@ __global__ void k_unpad(const float *__restrict__ G, int k_in, int n_out, int np
 hipError_t launch_unpad(const float *G, int k_in, int n_out, int np_, float *out, hipStream_t s) {
   const int total = k_in * n_out;
   hipLaunchKernelGGL(k_unpad, dim3((total + 255) / 256), dim3(256), 0, s, G, k_in, n_out, np_, out);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ Adam
-__global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
-                       float *__restrict__ v, int n, float lr, float b1, float b2, float eps, float c1,
-                       float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
-hipError_t launch_adam(float *p, const float *g, float *m, float *v, int n, float lr, float b1, float b2, float eps,
-                       int step, hipStream_t s) {
-  const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-  hipLaunchKernelGGL(k_adam, dim3((n + 255) / 256), dim3(256), 0, s, p, g, m, v, n, lr, b1, b2, eps, c1, c2);
   return hipGetLastError();
 }
 

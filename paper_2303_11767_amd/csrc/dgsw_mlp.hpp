@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace dgsw {
 
 constexpr int kFeatures = 108;   // 3 x 3 stencil x 3 variables x 4 modes
@@ -11,24 +13,13 @@ constexpr int kOut = 12;         // 3 variables x 4 modes of r = 1
 constexpr int kInPad = 128;      // feature width padded for the K loop
 constexpr int kOutPad = 32;      // output width padded for the N tiles
 
-enum { kEpiBiasGelu = 0, kEpiBias = 1, kEpiGeluGrad = 2, kEpiPlain = 3 };
+// offsets into the flat FP32 parameter vector
+constexpr int64_t kParams = (int64_t)kFeatures * kHidden + kHidden + (int64_t)kHidden * kHidden + kHidden +
+                            (int64_t)kHidden * kOut + kOut;
+constexpr int64_t oW1 = 0, ob1 = oW1 + (int64_t)kFeatures * kHidden, oW2 = ob1 + kHidden,
+                  ob2 = oW2 + (int64_t)kHidden * kHidden, oW3 = ob2 + kHidden,
+                  ob3 = oW3 + (int64_t)kHidden * kOut;
 
-struct GemmArgs {
-  const __bf16 *A, *B;
-  int M, N, K, lda, ldb;
-  const float *bias;   // kEpiBiasGelu, kEpiBias
-  const float *Zin;    // kEpiGeluGrad: pre-activations
-  float *Zout;         // kEpiBiasGelu: pre-activations out; kEpiGeluGrad: FP32 result out (optional)
-  void *C;             // BF16 (gelu variants) or FP32 result
-  int ldc;
-};
-hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, const GemmArgs &g, hipStream_t s);
-// Weight gradients C[M][N] = sum over k < K of A[k][m] B[k][n] (both operands
-// row-major over k): K split into gemm_splits(K) ranges of workgroups, the
-// partial products (partial: gemm_splits(K) * M * ldc floats) summed in order.
-constexpr int kMaxSplits = 64;
-int gemm_splits(int K);
-hipError_t launch_gemm_splitk(const GemmArgs &g, float *partial, hipStream_t s);
 // The learned stage's correction step, fused into the network kernel.
 struct CorrectionArgs {
   const void *L1;                // plain r = 1 right-hand side [E][12] (state dtype)
@@ -52,20 +43,48 @@ hipError_t launch_mlp_fused(int dtype, const void *q, int n_lon, int n_lat, cons
                             const float *X, int rows, const __bf16 *W1f, const __bf16 *W2f, const __bf16 *W3t,
                             const float *b1, const float *b2, const float *b3p, float *Y, hipStream_t s,
                             const CorrectionArgs *ca);
-hipError_t launch_prep_weights(const float *W, int k_in, int n_out, int kp, int np_, __bf16 *Wt, __bf16 *Wr,
-                               __bf16 *Wf, hipStream_t s);
-hipError_t launch_mse_grad(const float *Y, const float *T, unsigned mask_bits, int rows, int n_out, int ld,
-                           float scale, __bf16 *dY, float *dYf, float *partial, int *nblocks, hipStream_t s);
-// column sums over rows (partial: colsum_chunks(rows) * n floats)
-constexpr int kMaxColChunks = 256;
-int colsum_chunks(int rows);
-hipError_t launch_colsum(const float *G, int rows, int n, int ld, float *part, float *out, hipStream_t s);
-hipError_t launch_sum(const float *p, int n, float scale, float *out, hipStream_t s);
-hipError_t launch_to_bf16(const float *X, int rows, int n, int ldx, __bf16 *Xb, hipStream_t s);
-hipError_t launch_pad(const float *b, int n, int np_, float *out, hipStream_t s);
+// BF16 copies of the weights (null: not made) and the padded output biases.
+// *f: fragment order of the matrix whose rows are the layer's outputs, *rf:
+// whose rows are its inputs (backward); W3t[output][input] row-major.
+struct PrepWeights {
+  __bf16 *W1f, *W2f, *W3t, *W3f, *W2rf, *W3rf;
+  float *b3p;
+};
+hipError_t launch_prep_weights(const float *params, const PrepWeights &w, hipStream_t s);
+
+// The training step (kernels in dgsw_mlp.hip).  Factors of the weight
+// gradients, per 32 rows: blocks of 16 units in fragment order.
+constexpr int kMaxTrainBlocks = 512;                       // workgroups of the row kernel
+constexpr int kBiasPart = 2 * kHidden + 2 * kOutPad;       // a workgroup's bias-gradient sums
+constexpr int kMaxSplits = 64;                             // ranges of rows of the weight gradients
+constexpr int oG1 = 0, oG2 = kInPad * kHidden, oG3 = oG2 + kHidden * kHidden;
+constexpr int kGradPart = oG3 + kHidden * kOutPad;         // a range's weight-gradient sums
+int train_row_blocks(int rows);
+int train_splits(int rows);
+struct TrainRows {
+  const float *P, *X, *T;
+  int rows;
+  unsigned mask_bits;       // bit n: output n counts
+  float scale;              // 1 / (rows x outputs that count)
+  PrepWeights w;
+  __bf16 *Xf, *H1f, *H2f, *DYf, *D2f, *D1f;
+  float *bias_part, *se_part;
+};
+struct TrainDw {
+  const __bf16 *Xf, *H1f, *H2f, *DYf, *D2f, *D1f;
+  int chunks, per;          // 32-row chunks, and how many a range takes
+  float *part;              // [splits][kGradPart]
+};
+struct TrainUpdate {
+  const float *part, *bias_part, *se_part;
+  int splits, blocks;
+  float scale;
+  float *grads, *loss;      // optional
+  float *p, *m, *v;         // updated when lr > 0
+  float lr, b1, b2, eps, c1, c2;
+};
+hipError_t launch_train(const TrainRows &r, const TrainDw &d, const TrainUpdate &u, hipStream_t s);
 hipError_t launch_unpad(const float *G, int k_in, int n_out, int np_, float *out, hipStream_t s);
-hipError_t launch_adam(float *p, const float *g, float *m, float *v, int n, float lr, float b1, float b2, float eps,
-                       int step, hipStream_t s);
 hipError_t launch_features(int dtype, const void *q, int n_lon, int n_lat, const float *mean, const float *istd,
                            int ldx, __bf16 *X, hipStream_t s);
 hipError_t launch_features_f32(int dtype, const void *q, int n_lon, int n_lat, const float *mean, const float *istd,
