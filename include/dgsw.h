@@ -390,8 +390,9 @@ typedef struct {
   double lx, ly;        /* domain lengths, > 0                                         */
   double bx, by;        /* constant velocity beta, finite                              */
 } dg_adv_desc;
-/* Assembles the linear operator on the host (five (r+1)^2 x (r+1)^2 matrices:
- * the element and its four neighbours) and uploads it; *out NULL on failure. */
+/* Assembles the linear operator on the host (six (r+1) x (r+1) matrices: per
+ * direction the element and its two neighbours) and uploads it; *out NULL on
+ * failure. */
 int dg_adv_init(const dg_adv_desc *desc, void *hip_stream, dg_adv **out);
 int dg_adv_free(dg_adv *adv);
 int dg_adv_state_size(const dg_adv *adv, int64_t *n_values);   /* E * N */

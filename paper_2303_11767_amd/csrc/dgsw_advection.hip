@@ -6,12 +6,14 @@
 // Legendre tensor basis, (r+1)-point Gauss-Legendre volume and edge rules,
 // the weak form of equation "dg_parts", the Rusanov flux of equation
 // "rusanov" (for f(u) = b u it is the upwind flux) and the mass matrix
-// (dx dy / 4) I.  Because the operator is linear and the mesh uniform, the host
-// assembles it once into five N x N matrices, one per stencil slot (the
-// element and its east, west, north and south neighbours); a stage is then
-// dq_e/dt = sum_k A_k q_{neighbour k of e}, a dense contraction of length 5N
-// per output mode.  Work unit: one (element, mode) per lane; the matrices
-// and the workgroup's stencil rows are staged in LDS.
+// (dx dy / 4) I.  The operator is linear, the mesh uniform, and the rules are
+// exact for products of two basis functions, so the terms of the x direction
+// act on the x degree alone and leave the y degree alone, and conversely: the
+// host assembles six n x n matrices (n = r + 1), per direction that of the
+// element and of its two neighbours, and with q_e as the matrix [b][a]
+//   dq_e/dt = q_e Sx^T + q_east Ex^T + q_west Wx^T + Sy q_e + Ny q_north + Zy q_south,
+// 6n multiply-adds per output mode (the dense form of length 5 n^2, five
+// n^2 x n^2 matrices, took 11.7 us a stage at 160x160 r = 3 FP64).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -32,19 +34,19 @@ struct dg_adv {
   int np = 0, N = 0, E = 0;
   int64_t state_n = 0;
   size_t elem_bytes = 0;
-  void *d_ops = nullptr;     // [5][N][N] in the state dtype
+  void *d_ops = nullptr;     // [6][np][np] in the state dtype
 };
 
 namespace {
 
 constexpr int kSlots = 5;    // self, east, west, north, south
+constexpr int kOps = 6;      // Sx, Ex, Wx, Sy, Ny, Zy
 
-// Residual contribution, to every output mode of one element, of a single
-// unit coefficient n in stencil slot `slot` (so column n of A_slot): the
-// volume term for the element itself and the upwind surface terms of the edge
-// shared with that neighbour.  Host FP64; M^-1 = 4 / (dx dy) applied at the end.
-void assemble(int np, double dx, double dy, double bx, double by, std::vector<double> &A) {
-  const int N = np * np;
+// One direction: the element's, the next and the previous neighbour's matrix
+// [m][k] (output degree, input degree) of du/dt + b du/dx = 0 on elements of
+// width d, with the upwind flux: volume term (2/d) b int u phi', minus the flux
+// b u_upwind times phi at the two ends.
+void assemble(int np, double d, double b, double *self, double *next, double *prev) {
   std::vector<double> x, w;
   dgsw::gauss_legendre(np, x, w);
   std::vector<double> P(np * np), D(np * np), Pp(np), Pm(np);
@@ -57,42 +59,22 @@ void assemble(int np, double dx, double dy, double bx, double by, std::vector<do
   for (int a = 0; a < np; ++a) Pp[a] = pv[a];
   dgsw::legendre_onb(np - 1, -1.0, pv, dv);
   for (int a = 0; a < np; ++a) Pm[a] = pv[a];
-  A.assign((size_t)kSlots * N * N, 0.0);
-  auto at = [&](int slot, int m, int n) -> double & { return A[((size_t)slot * N + m) * N + n]; };
-  const double minv = 4.0 / (dx * dy);
-  for (int m = 0; m < N; ++m) {
-    const int am = m % np, bm = m / np;
-    for (int n = 0; n < N; ++n) {
-      const int an = n % np, bn = n / np;
-      // volume: (dy/2) int bx u dphi/dxi + (dx/2) int by u dphi/deta, by quadrature
+  const double c = 2.0 / d;
+  for (int m = 0; m < np; ++m)
+    for (int k = 0; k < np; ++k) {
       double vol = 0.0;
-      for (int s = 0; s < np; ++s)
-        for (int p = 0; p < np; ++p) {
-          const double u = P[p * np + an] * P[s * np + bn];
-          vol += w[p] * w[s] * u *
-                 (0.5 * dy * bx * D[p * np + am] * P[s * np + bm] + 0.5 * dx * by * P[p * np + am] * D[s * np + bm]);
-        }
-      at(0, m, n) += minv * vol;
-      // x edges: flux bx u_upwind at the edge nodes eta_s, weight (dy/2) w_s
-      for (int s = 0; s < np; ++s) {
-        const double ws = 0.5 * dy * w[s] * P[s * np + bm] * P[s * np + bn];
-        // east edge (xi = +1 of this element, -1 of the east neighbour): - F^ phi_m(+1)
-        if (bx >= 0.0) at(0, m, n) -= minv * ws * bx * Pp[an] * Pp[am];
-        else at(1, m, n) -= minv * ws * bx * Pm[an] * Pp[am];
-        // west edge (xi = -1 of this element, +1 of the west neighbour): + F^ phi_m(-1)
-        if (bx >= 0.0) at(2, m, n) += minv * ws * bx * Pp[an] * Pm[am];
-        else at(0, m, n) += minv * ws * bx * Pm[an] * Pm[am];
-      }
-      // y edges, the same with by, dx and eta
-      for (int p = 0; p < np; ++p) {
-        const double wp = 0.5 * dx * w[p] * P[p * np + am] * P[p * np + an];
-        if (by >= 0.0) at(0, m, n) -= minv * wp * by * Pp[bn] * Pp[bm];
-        else at(3, m, n) -= minv * wp * by * Pm[bn] * Pp[bm];
-        if (by >= 0.0) at(4, m, n) += minv * wp * by * Pp[bn] * Pm[bm];
-        else at(0, m, n) += minv * wp * by * Pm[bn] * Pm[bm];
+      for (int p = 0; p < np; ++p) vol += w[p] * D[p * np + m] * P[p * np + k];
+      const int i = m * np + k;
+      if (b >= 0.0) {
+        self[i] = c * b * (vol - Pp[m] * Pp[k]);
+        next[i] = 0.0;
+        prev[i] = c * b * Pm[m] * Pp[k];
+      } else {
+        self[i] = c * b * (vol + Pm[m] * Pm[k]);
+        next[i] = -c * b * Pp[m] * Pm[k];
+        prev[i] = 0.0;
       }
     }
-  }
 }
 
 struct AdvArgs {
@@ -102,68 +84,165 @@ struct AdvArgs {
   double c0, c1, ce, dt, ca, cb;
 };
 
-// One lane per (element, output mode), G = 256 / N consecutive elements per
-// workgroup.  The five matrices and the G elements' five stencil rows are
-// staged in LDS (the rows with coalesced loads, one value per lane per slot),
-// then every lane contracts its output row of each matrix with its element's
-// rows: 5N multiply-adds from LDS.
-template <typename T, int N>
+// The combination's operands at one value, loaded with the stage's first loads
+// (a later load would be one more trip to memory), and the combination.
+template <typename T>
+struct AdvOperands {
+  T q0, qa, qb;
+};
+template <typename T>
+__device__ __forceinline__ AdvOperands<T> adv_operands(size_t o, const T *q0, const T *qa, const T *qb, int combine, T c0) {
+  AdvOperands<T> x;
+  x.q0 = combine == 2 || (combine == 1 && c0 != T(0)) ? q0[o] : T(0);
+  x.qa = combine == 2 && qa ? qa[o] : x.q0;
+  x.qb = combine == 2 && qb ? qb[o] : x.q0;
+  return x;
+}
+template <typename T>
+__device__ __forceinline__ T adv_combine(T acc, T qo, const AdvOperands<T> &x, int combine, T c0, T c1, T ce, T dt,
+                                         T ca, T cb) {
+  if (combine == 2)
+    return x.q0 + dt * acc + (c1 * (qo - x.q0) + (ca * (x.qa - x.q0) + cb * (x.qb - x.q0)));
+  if (combine == 1) {
+    const T y = qo + dt * acc;
+    return y + c0 * (x.q0 - y) + ce * y;
+  }
+  return acc;
+}
+
+// Workgroups are dispatched round-robin over the 8 XCDs; renumbered so that
+// each XCD takes one contiguous range of rows (its L2 then holds them and their
+// neighbours).
+__device__ __forceinline__ int adv_block() {
+  const int nb = gridDim.x, x = blockIdx.x & 7, per = nb >> 3, rem = nb & 7;
+  return x * per + (x < rem ? x : rem) + (blockIdx.x >> 3);
+}
+
+// The five stencil elements of element e = j nx + i.
+__device__ __forceinline__ void adv_stencil(int e, int nx, int ny, int (&nb)[kSlots]) {
+  const int j = (int)((unsigned)e / (unsigned)nx), i = e - j * nx;
+  nb[0] = e;
+  nb[1] = i + 1 == nx ? e + 1 - nx : e + 1;
+  nb[2] = i == 0 ? e - 1 + nx : e - 1;
+  nb[3] = j + 1 == ny ? i : e + nx;
+  nb[4] = j == 0 ? (ny - 1) * nx + i : e - nx;
+}
+
+// One lane per (element, output mode (b, a)), G = 256 / N consecutive elements
+// per workgroup.  The matrices and the G elements' five stencil rows are staged
+// in LDS (the rows with coalesced loads, one value per lane per slot).
+template <typename T, int NP>
 __global__ __launch_bounds__(256) void k_adv_stage(const T *__restrict__ ops, const T *__restrict__ q,
                                                    const T *q0, const T *qa, const T *qb, T *out, int nx, int ny,
                                                    int combine, T c0, T c1, T ce, T dt, T ca, T cb) {
-  constexpr int G = 256 / N;
+  constexpr int N = NP * NP, G = 256 / N;
   // padded strides: rows of different output modes / elements start in
   // different LDS banks
-  constexpr int LA = N + 1, LQ = kSlots * N + 1;
-  __shared__ T sA[kSlots * N * LA];
+  constexpr int LA = NP + 1, LQ = kSlots * N + 1;
+  __shared__ T sA[kOps * NP * LA];
   __shared__ T sQ[G * LQ];
-  for (int k = threadIdx.x; k < kSlots * N * N; k += 256) sA[(k / N) * LA + k % N] = ops[k];
+  for (int k = threadIdx.x; k < kOps * N; k += 256) sA[(k / NP) * LA + k % NP] = ops[k];
   const int64_t E = (int64_t)nx * ny;
-  const int g = threadIdx.x / N, m = threadIdx.x - g * N;
-  const int64_t e64 = (int64_t)blockIdx.x * G + g;
+  const int g = threadIdx.x / N, m = threadIdx.x - g * N, b = m / NP, a = m - b * NP;
+  const int64_t e64 = (int64_t)adv_block() * G + g;
   const bool live = g < G && e64 < E;
   const int e = live ? (int)e64 : 0;
-  const int j = e / nx, i = e - j * nx;
+  const size_t o = (size_t)e * N + m;
+  AdvOperands<T> x{T(0), T(0), T(0)};
   if (g < G) {
-    const int nb[kSlots] = {e, j * nx + (i + 1 == nx ? 0 : i + 1), j * nx + (i == 0 ? nx - 1 : i - 1),
-                            (j + 1 == ny ? 0 : j + 1) * nx + i, (j == 0 ? ny - 1 : j - 1) * nx + i};
+    int nb[kSlots];
+    adv_stencil(e, nx, ny, nb);
+    T v[kSlots];
 #pragma unroll
-    for (int k = 0; k < kSlots; ++k) sQ[g * LQ + k * N + m] = q[(size_t)nb[k] * N + m];
+    for (int k = 0; k < kSlots; ++k) v[k] = q[(size_t)nb[k] * N + m];
+    x = adv_operands<T>(o, q0, qa, qb, combine, c0);
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) sQ[g * LQ + k * N + m] = v[k];
   }
   __syncthreads();
   if (!live) return;
+  const T *S = sQ + g * LQ;
+  const T *rx = S + b * NP, *ry = S + a;               // row b (x degrees) and column a (y degrees)
   T acc = T(0);
 #pragma unroll
-  for (int k = 0; k < kSlots; ++k) {
-    const T *row = sA + (k * N + m) * LA;
-    const T *src = sQ + g * LQ + k * N;
-#pragma unroll
-    for (int n = 0; n < N; ++n) acc += row[n] * src[n];
+  for (int k = 0; k < NP; ++k) {
+    acc += sA[(0 * NP + a) * LA + k] * rx[k];
+    acc += sA[(1 * NP + a) * LA + k] * rx[N + k];
+    acc += sA[(2 * NP + a) * LA + k] * rx[2 * N + k];
+    acc += sA[(3 * NP + b) * LA + k] * ry[k * NP];
+    acc += sA[(4 * NP + b) * LA + k] * ry[3 * N + k * NP];
+    acc += sA[(5 * NP + b) * LA + k] * ry[4 * N + k * NP];
   }
-  const size_t o = (size_t)e * N + m;
-  const T qo = sQ[g * LQ + m];
-  T res;
-  if (combine == 2) {
-    const T b0 = q0[o];
-    res = b0 + dt * acc + (c1 * (qo - b0) + ((qa ? ca * (qa[o] - b0) : T(0)) + (qb ? cb * (qb[o] - b0) : T(0))));
-  } else if (combine == 1) {
-    const T y = qo + dt * acc;
-    res = y + c0 * ((c0 != T(0) ? q0[o] : T(0)) - y) + ce * y;
-  } else {
-    res = acc;
-  }
-  out[o] = res;
+  out[o] = adv_combine<T>(acc, S[m], x, combine, c0, c1, ce, dt, ca, cb);
 }
 
-template <typename T, int N>
+// r = 3 in FP64: each of the six terms is one v_mfma_f64_4x4x4 block per
+// element, four elements per wavefront (lane l: element (l / 4) % 4, entry
+// (x, y) = (l / 16, l % 4) of every 4 x 4 array; A[i = y][k = x], B[k = x][j = y],
+// result [x][y]).  The stencil is loaded in memory order (a wavefront's 64
+// lanes read 512 contiguous bytes a slot), turned to the operand layouts
+// through LDS, and so is the result.  160x160: 11.9 -> 4.5 us a stage, of which
+// the launch is about half; before the XCD renumbering and with the
+// combination's operands loaded after the products 5.1.
+__global__ __launch_bounds__(256) void k_adv_stage_m4(const double *__restrict__ ops, const double *__restrict__ q,
+                                                      const double *q0, const double *qa, const double *qb,
+                                                      double *out, int nx, int ny, int combine, double c0, double c1,
+                                                      double ce, double dt, double ca, double cb) {
+  constexpr int LE = 24, LS = 4 * LE;                  // padded strides of an element and a slot
+  __shared__ double sA[kOps * 16];
+  __shared__ double sQ[4][kSlots * LS];
+  if (threadIdx.x < kOps * 16) sA[threadIdx.x] = ops[threadIdx.x];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int E = nx * ny;
+  const int e_raw = adv_block() * 16 + wv * 4 + (lane >> 4), m = lane & 15;
+  const bool live = e_raw < E;
+  const int e = live ? e_raw : E - 1;
+  const size_t o = (size_t)e * 16 + m;
+  double *S = sQ[wv];
+  double qo;
+  AdvOperands<double> op;
+  {
+    int nb[kSlots];
+    adv_stencil(e, nx, ny, nb);
+    double v[kSlots];
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) v[k] = q[(size_t)nb[k] * 16 + m];
+    op = adv_operands<double>(o, q0, qa, qb, combine, c0);
+    qo = v[0];
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) S[k * LS + (lane >> 4) * LE + m] = v[k];
+  }
+  __syncthreads();
+  const int x = lane >> 4, y = lane & 3, at = ((lane >> 2) & 3) * LE;
+  const int n = at + 4 * x + y, t = at + 4 * y + x, c = 4 * y + x;
+  double acc = __builtin_amdgcn_mfma_f64_4x4x4f64(S[t], sA[c], 0.0, 0, 0, 0);
+  double acy = __builtin_amdgcn_mfma_f64_4x4x4f64(sA[48 + c], S[n], 0.0, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f64_4x4x4f64(S[LS + t], sA[16 + c], acc, 0, 0, 0);
+  acy = __builtin_amdgcn_mfma_f64_4x4x4f64(sA[64 + c], S[3 * LS + n], acy, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f64_4x4x4f64(S[2 * LS + t], sA[32 + c], acc, 0, 0, 0);
+  acy = __builtin_amdgcn_mfma_f64_4x4x4f64(sA[80 + c], S[4 * LS + n], acy, 0, 0, 0);
+  __syncthreads();
+  S[n] = acc + acy;
+  __syncthreads();
+  if (!live) return;
+  out[o] = adv_combine<double>(S[(lane >> 4) * LE + m], qo, op, combine, c0, c1, ce, dt, ca, cb);
+}
+
+template <typename T, int NP>
 hipError_t launch_adv_t(const dg_adv *a, const AdvArgs &g, hipStream_t s) {
-  constexpr int G = 256 / N;
+  constexpr int G = 256 / (NP * NP);
   const int64_t E = (int64_t)g.nx * g.ny;
   const dim3 grid((unsigned)((E + G - 1) / G)), block(256);
-  hipLaunchKernelGGL((k_adv_stage<T, N>), grid, block, 0, s, static_cast<const T *>(a->d_ops),
-                     static_cast<const T *>(g.q), static_cast<const T *>(g.q0), static_cast<const T *>(g.qa),
-                     static_cast<const T *>(g.qb), static_cast<T *>(g.out), g.nx, g.ny, g.combine, T(g.c0), T(g.c1),
-                     T(g.ce), T(g.dt), T(g.ca), T(g.cb));
+  const T *ops = static_cast<const T *>(a->d_ops), *q = static_cast<const T *>(g.q), *q0 = static_cast<const T *>(g.q0);
+  const T *qa = static_cast<const T *>(g.qa), *qb = static_cast<const T *>(g.qb);
+  T *out = static_cast<T *>(g.out);
+  if constexpr (sizeof(T) == 8 && NP == 4)
+    hipLaunchKernelGGL(k_adv_stage_m4, grid, block, 0, s, ops, q, q0, qa, qb, out, g.nx, g.ny, g.combine, g.c0, g.c1,
+                       g.ce, g.dt, g.ca, g.cb);
+  else
+    hipLaunchKernelGGL((k_adv_stage<T, NP>), grid, block, 0, s, ops, q, q0, qa, qb, out, g.nx, g.ny, g.combine,
+                       T(g.c0), T(g.c1), T(g.ce), T(g.dt), T(g.ca), T(g.cb));
   return hipGetLastError();
 }
 
@@ -171,12 +250,12 @@ template <typename T>
 hipError_t launch_adv_d(const dg_adv *a, const AdvArgs &g, hipStream_t s) {
   switch (a->np) {
     case 1: return launch_adv_t<T, 1>(a, g, s);
-    case 2: return launch_adv_t<T, 4>(a, g, s);
-    case 3: return launch_adv_t<T, 9>(a, g, s);
-    case 4: return launch_adv_t<T, 16>(a, g, s);
-    case 5: return launch_adv_t<T, 25>(a, g, s);
-    case 6: return launch_adv_t<T, 36>(a, g, s);
-    case 7: return launch_adv_t<T, 49>(a, g, s);
+    case 2: return launch_adv_t<T, 2>(a, g, s);
+    case 3: return launch_adv_t<T, 3>(a, g, s);
+    case 4: return launch_adv_t<T, 4>(a, g, s);
+    case 5: return launch_adv_t<T, 5>(a, g, s);
+    case 6: return launch_adv_t<T, 6>(a, g, s);
+    case 7: return launch_adv_t<T, 7>(a, g, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -218,8 +297,9 @@ int dg_adv_init(const dg_adv_desc *d, void *hip_stream, dg_adv **out) {
   a->E = d->nx * d->ny;
   a->state_n = (int64_t)a->E * a->N;
   a->elem_bytes = d->dtype == DG_F64 ? 8 : 4;
-  std::vector<double> A;
-  assemble(a->np, d->lx / d->nx, d->ly / d->ny, d->bx, d->by, A);
+  std::vector<double> A((size_t)kOps * a->N);
+  assemble(a->np, d->lx / d->nx, d->bx, &A[0], &A[a->N], &A[2 * a->N]);
+  assemble(a->np, d->ly / d->ny, d->by, &A[3 * a->N], &A[4 * a->N], &A[5 * a->N]);
   std::vector<unsigned char> h(A.size() * a->elem_bytes);
   if (d->dtype == DG_F64) {
     std::memcpy(h.data(), A.data(), h.size());
