@@ -99,10 +99,21 @@ hipError_t launch_ens_stage_np(int dtype, int np, int layout, int wpb, const Ens
 
 // Line layout: wavefronts per row.
 int waves_per_row(int np, int n_lon);
-// Half layout: elements of one wavefront (r = 3 in FP64: of one group of the
-// matrix-core stage, dgsw_stage_m4.hpp).
+// Half layout at r = 3 in FP64 (dgsw_stage_m4.hpp): groups of four elements.
 constexpr int kM4Elems = 4;
-inline int half_elems(int dtype, int np) { return dtype == 0 && np == 4 ? kM4Elems : 64 / (2 * np); }
+// Groups of a mesh: every four elements across row ends, or (rows of fewer
+// than four) one per row.
+inline int m4_groups(int n_lon, int n_lat) {
+  return n_lon >= kM4Elems ? (int)(((long long)n_lon * n_lat + kM4Elems - 1) / kM4Elems) : n_lat;
+}
+// Groups per wavefront: one where the mesh fills at most three wavefronts per
+// SIMD (more in flight beats the prefetch: 150x75 6.2 us a stage with one, 6.6
+// with two); then two (180x90 7.6 / 7.2 / 8.1 us with 1 / 2 / 4, 360x180 22.3 /
+// 19.9 / 20.1); four from about 25000 groups (512x256 40.4 / 36.1 / 35.2 / 38.9
+// with 1 / 2 / 4 / 6), six from 131072 (1440x720 323 / 295 / 284 / 281).
+inline int m4_loop(long long groups) {
+  return groups <= 3200 ? 1 : (groups <= 24576 ? 2 : (groups <= 131072 ? 4 : 6));
+}
 
 // Upload helpers: convert FP64 host tables to the device layouts.
 // Returns the number of bytes of each table for (dtype, np).

@@ -7,19 +7,23 @@ namespace dgsw {
 
 // ------------------------------------------------------------------ ensemble
 // LDS of one wavefront for any order up to NPMAX
-constexpr int lds_tab(int k) { return (2 * k * k + k + 63) / 64 * 64; }   // Shape<T, k>::TB
-constexpr int lds_sh(int k) {
-  return (64 / k + 1) * ((3 * (k + 2) * k + 12 * k) > (6 * k * k + 6 * k) ? (3 * (k + 2) * k + 12 * k)
-                                                                           : (6 * k * k + 6 * k));
-}
-constexpr int lds_max_tab(int npmax) { return npmax == 0 ? 0 : (lds_tab(npmax) > lds_max_tab(npmax - 1) ? lds_tab(npmax) : lds_max_tab(npmax - 1)); }
-constexpr int lds_max_sh(int npmax) { return npmax == 0 ? 0 : (lds_sh(npmax) > lds_max_sh(npmax - 1) ? lds_sh(npmax) : lds_max_sh(npmax - 1)); }
+// strips where the mesh kernel takes them at any size
+template <typename T, int NP>
+constexpr bool ens_strips = Shape<T, NP>::UNALIGNED && sizeof(T) == 4;
+template <typename T, int NPMAX>
+struct LdsMax {
+  using S_ = Shape<T, NPMAX>;
+  static constexpr int tab = S_::cmax(S_::TB, LdsMax<T, NPMAX - 1>::tab);
+  static constexpr int sh = S_::cmax(S_::wave(ens_strips<T, NPMAX>), LdsMax<T, NPMAX - 1>::sh);
+};
+template <typename T>
+struct LdsMax<T, 0> {
+  static constexpr int tab = 0, sh = 0;
+};
 
 template <typename T, int NP, int CM>
 __device__ __forceinline__ void ens_case(const EnsItem &m, const unsigned char *__restrict__ tabs, const T *q,
                                          const T *q0, T *out, int combine, T c0, T ce, int lane, T *tab, T *sh) {
-  static_assert(Shape<T, NP>::TB <= lds_tab(NP) && (Shape<T, NP>::GPW + 1) * Shape<T, NP>::SH <= lds_sh(NP),
-                "the fused kernel's LDS slices hold this order's");
   StageArgs<T, NP> A;
   A.q = q + m.off;
   A.q0 = q0 ? q0 + m.off : nullptr;
@@ -38,7 +42,7 @@ __device__ __forceinline__ void ens_case(const EnsItem &m, const unsigned char *
   A.c1 = T(0);
   A.ce = ce;
   A.dt = T(m.dt);
-  stage_wave<T, NP, CM>(A, m.j, m.seg, lane, tab, sh);
+  stage_wave<T, NP, CM, ens_strips<T, NP>>(A, m.j, m.seg, lane, tab, sh);
 }
 
 // One launch per Runge-Kutta stage for a whole ensemble of meshes of different
@@ -54,8 +58,8 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage(const T *__restrict__ q,
                                                         const EnsItem *__restrict__ items,
                                                         const int *__restrict__ bounds, int combine,
                                                         T c0, T ce) {
-  __shared__ T tab_all[WPB][lds_max_tab(NPMAX)];
-  __shared__ T sh_all[WPB][lds_max_sh(NPMAX)];
+  __shared__ T tab_all[WPB][LdsMax<T, NPMAX>::tab];
+  __shared__ __attribute__((aligned(16))) T sh_all[WPB][LdsMax<T, NPMAX>::sh];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   T *tab = tab_all[wv], *sh = sh_all[wv];
   const int part = xcd_block(blockIdx.x, gridDim.x);
@@ -116,7 +120,7 @@ struct EnsLds {
   static constexpr bool G4 = M4<T, NP> && LAY == 1;
   static constexpr int TB = G4 ? 2 : (LAY == 0 ? Shape<T, NP>::TB : ShapeH2<T, NP>::TB);
   static constexpr int SH = G4 ? kM4Lds
-                               : (LAY == 0 ? (Shape<T, NP>::GPW + 1) * Shape<T, NP>::SH
+                               : (LAY == 0 ? Shape<T, NP>::wave(ens_strips<T, NP>)
                                            : ShapeH2<T, NP>::SLOTS * ShapeH2<T, NP>::SH);
 };
 
@@ -127,7 +131,14 @@ __device__ __forceinline__ void ens_item(const EnsItem &m, const unsigned char *
     ens_case<T, NP, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh);
   } else if constexpr (M4<T, NP>) {
     const StageArgs<T, NP> A = ens_args<T, NP>(m, tabs, q, q0, out, combine, c0, ce);
-    m4_one<CM>(A, M4Group{m.seg, m.e_end, m.j, 0}, lane, (lds_double *)sh);
+    m4_run<CM, false>(
+        A, (m.e_end - m.seg + kM4Elems - 1) / kM4Elems,
+        [&](int k) {
+          const int e0 = m.seg + kM4Elems * k;
+          return M4Group{e0, m.e_end, k == 0 ? m.j : (int)((unsigned)e0 / (unsigned)m.n_lon), 0};
+        },
+        lane, (lds_double *)sh);
+    m4_have_read();   // before the wavefront's next item arrives
   } else {
     stage_wave_h2<T, NP, CM, true>(ens_args<T, NP>(m, tabs, q, q0, out, combine, c0, ce), m.j, m.seg, m.e_end, lane,
                                    tab, sh);

@@ -35,7 +35,7 @@ struct dg_ens {
   unsigned char *d_tabs = nullptr;
   std::vector<long long> tab_glob, tab_rows;   // per member
   int bounds_cap = 0;
-  int wpb = 4, parts = 0, fused = 0, flat = 1;
+  int wpb = 1, parts = 0, fused = 0, flat = 1;
   std::vector<int> layout;               // per member: DG_KERNEL_LINE or DG_KERNEL_HALF
   // members of one order and layout form one contiguous group of the sorted work list
   struct Group { int np, lay, begin, end, parts, bounds_off; double cost; };
@@ -72,6 +72,12 @@ int build_items(dg_ens *e) {
   std::vector<dgsw::EnsItem> items;
   std::vector<double> cost;
   std::vector<std::pair<int, int>> key;
+  // the matrix-core stage's groups per wavefront: as a mesh of all such members
+  long long groups = 0;
+  for (int m = 0; m < e->n; ++m)
+    if (e->layout[m] == DG_KERNEL_HALF && e->dtype == 0 && e->members[m]->np == 4)
+      groups += dgsw::m4_groups(e->members[m]->d.n_lon, e->members[m]->d.n_lat);
+  const int m4_loop = dgsw::m4_loop(groups);
   for (int m = 0; m < e->n; ++m) {
     const dg_ctx *c = e->members[m];
     const int lay = e->layout[m];
@@ -103,10 +109,11 @@ int build_items(dg_ens *e) {
       for (int j = 0; j < n_lat; ++j)
         for (int sg = 0; sg < segs; ++sg) add(j, sg, 0, np3);
     } else {
-      const int gpw = dgsw::half_elems(e->dtype, c->np);
+      const bool m4 = e->dtype == 0 && c->np == 4;
+      const int gpw = m4 ? dgsw::kM4Elems * m4_loop : 64 / (2 * c->np);
       const double w = np3 * 2.0 * c->np * gpw / 128.0;
-      if (gpw <= n_lon && n_lon % gpw != 0) {      // packed across row ends
-        for (int e0 = 0; e0 < E; e0 += gpw) add(e0 / n_lon, e0, E, w);
+      if (gpw <= n_lon && (m4 || n_lon % gpw != 0)) {      // packed across row ends
+        for (int e0 = 0; e0 < E; e0 += gpw) add(e0 / n_lon, e0, std::min(E, e0 + gpw), w);
       } else {
         const int segs = (n_lon + gpw - 1) / gpw;
         for (int j = 0; j < n_lat; ++j)
@@ -331,7 +338,10 @@ int dg_ens_init(const dg_mesh_desc *members, int32_t n_members, void *hip_stream
       return rc;
     }
   }
-  int rc = upload_schedule(e, 4, 0, 0);
+  // flat, one wavefront per workgroup: 64 members of orders 2..4 up to 360x180,
+  // FP32 1096 us a step (two 1114, four 1190: a workgroup's LDS is granted as a
+  // whole), 24 members FP64 778 (780, 847)
+  int rc = upload_schedule(e, 1, 0, 0);
   if (rc != DG_OK) {
     ens_release(e);
     return rc;

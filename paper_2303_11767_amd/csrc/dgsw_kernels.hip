@@ -45,50 +45,28 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * WPB) v
 template <int CM, bool MORE>
 __global__ __attribute__((amdgpu_waves_per_eu(MORE ? 3 : 4))) __launch_bounds__(64) void k_dg_stage_m4(
     StageArgs<double, 4> A, int per, int loop) {
-  __shared__ __attribute__((aligned(16))) double sh_[kM4Lds];
-  lds_double *sh = (lds_double *)sh_;
-  const int lane = threadIdx.x;
+  __shared__ __attribute__((aligned(16))) double sh[kM4Lds];
   const int all = per * A.levels;
-  int n = xcd_block(blockIdx.x, gridDim.x) * loop;
-  const int end = n + loop < all ? n + loop : all;
-  if (n >= end) return;
-  const bool use_q0 = CM == 2 || (CM == 1 && A.c0 != 0.0);
-  auto group = [&](int m) {
-    const int lev = A.levels == 1 ? 0 : (unsigned)m / (unsigned)per;
-    return m4_group(A.n_lon, A.n_lat, m - lev * per, lev * A.lstride);
-  };
-  const M4Tab t = m4_tables(A.gt, lane);
-  M4Group g = group(n);
-  m4_fetch(A, g, use_q0, lane, sh);
-  m4_fetched();
-  for (;;) {
-    M4Data d = m4_read(A, g, use_q0, lane, sh);
-    const M4More o = m4_more<CM, MORE>(A, g, lane);
-    m4_have_read();
-    M4Group next = g;
-    ++n;
-    if (n < end) {
-      next = group(n);
-      m4_fetch(A, next, use_q0, lane, sh);
-    }
-    m4_compute<CM>(A, t, d, o, lane, sh);
-    wave_sync();
-    // the next group's data before the stores are queued behind them
-    if (n < end) m4_fetched();
-    m4_store(A, g, lane, sh);
-    if (n >= end) break;
-    g = next;
-  }
+  const int n0 = xcd_block(blockIdx.x, gridDim.x) * loop;
+  const int count = n0 + loop < all ? loop : all - n0;
+  if (count < 1) return;
+  m4_run<CM, MORE>(
+      A, count,
+      [&](int k) {
+        const int n = n0 + k, lev = A.levels == 1 ? 0 : (unsigned)n / (unsigned)per;
+        return m4_group(A.n_lon, A.n_lat, n - lev * per, lev * A.lstride);
+      },
+      threadIdx.x, (lds_double *)sh);
 }
 
-template <typename T, int NP, int WPB, int CM>
+template <typename T, int NP, int WPB, int CM, bool STRIPS>
 __global__ __launch_bounds__(64 * WPB) void k_dg_stage(StageArgs<T, NP> A, int segs) {
   using S_ = Shape<T, NP>;
   // WPB independent wavefronts per workgroup (fewer workgroups to dispatch on
   // large meshes); each wavefront has its own LDS slice and never waits for
   // another one
   __shared__ T tab_all[WPB][S_::TB];
-  __shared__ T sh_all[WPB][(S_::GPW + 1) * S_::SH];
+  __shared__ __attribute__((aligned(16))) T sh_all[WPB][S_::wave(STRIPS)];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int blk = xcd_block(blockIdx.x, gridDim.x) * WPB + wv;
   const int per = segs * A.n_lat;            // wavefronts of one layer
@@ -96,7 +74,7 @@ __global__ __launch_bounds__(64 * WPB) void k_dg_stage(StageArgs<T, NP> A, int s
   const int lev = blk / per;
   blk -= lev * per;
   const int j = blk / segs;
-  stage_wave<T, NP, CM>(layer_args(A, lev), j, blk - j * segs, threadIdx.x & 63, tab_all[wv],
+  stage_wave<T, NP, CM, STRIPS>(layer_args(A, lev), j, blk - j * segs, threadIdx.x & 63, tab_all[wv],
                         sh_all[wv]);
 }
 
@@ -192,15 +170,6 @@ static StageArgs<T, NP> stage_args(const StageLaunch &a) {
   return A;
 }
 
-// Groups per wavefront: one where the mesh fills at most three wavefronts per
-// SIMD (more in flight beats the prefetch: 150x75 6.2 us a stage with one, 6.6
-// with two); then two (180x90 7.6 / 7.2 / 8.1 us with 1 / 2 / 4, 360x180 22.3 /
-// 19.9 / 20.1); four from about 25000 groups (512x256 40.4 / 36.1 / 35.2 / 38.9
-// with 1 / 2 / 4 / 6), six from 131072 (1440x720 323 / 295 / 284 / 281).
-static int m4_loop(long long groups) {
-  return groups <= 3200 ? 1 : (groups <= 24576 ? 2 : (groups <= 131072 ? 4 : 6));
-}
-
 template <typename T, int NP>
 static hipError_t launch_stage_t(const StageLaunch &a, hipStream_t s) {
   if (a.levels < 1) return hipErrorInvalidValue;
@@ -253,24 +222,39 @@ static hipError_t launch_stage_t(const StageLaunch &a, hipStream_t s) {
   constexpr int GPW = Shape<T, NP>::GPW;
   const int segs = (a.n_lon + GPW - 1) / GPW;
   const int waves = segs * a.n_lat * a.levels;
+  // Strips (rows that are not 16-byte aligned): in FP32 always, in FP64, where
+  // their LDS costs wavefronts, on meshes that fill the GPU several times.  Stage
+  // times, rows / strips, 720x360: r = 2 FP32 29.6 / 26.6 us, r = 4 94.9 / 74.5,
+  // r = 5 132 / 108, FP64 r = 2 62.4 / 51.9, r = 4 179 / 158; FP64 r = 2 360x180 (3240
+  // wavefronts) 18.2 / 18.9, r = 4 360x180 (5400) 48.1 / 45.7, 180x90 (1350) 15.5 /
+  // 15.8; rows that are aligned are faster as rows (r = 3 FP32 38.2 / 41.3).  One
+  // wavefront per workgroup then (their LDS, r = 5 FP32 720x360 134 us with four);
+  // with rows four on large meshes.
   const bool big = waves >= 4096;
-  const dim3 grid(big ? (waves + 3) / 4 : waves), block(big ? 256 : 64);
+  constexpr bool U = Shape<T, NP>::UNALIGNED;
+#define DGSW_LINE_K(W_, CM_, ST_) \
+  hipLaunchKernelGGL((k_dg_stage<T, NP, W_, CM_, ST_>), dim3((waves + W_ - 1) / W_), dim3(64 * W_), 0, s, A, segs)
+#define DGSW_LINE(CM_)                                    \
+  do {                                                    \
+    if constexpr (U && sizeof(T) == 4) {                  \
+      DGSW_LINE_K(1, CM_, true);                          \
+    } else if constexpr (U) {                             \
+      if (big) DGSW_LINE_K(1, CM_, true);                 \
+      else DGSW_LINE_K(1, CM_, false);                    \
+    } else {                                              \
+      if (big) DGSW_LINE_K(4, CM_, false);                \
+      else DGSW_LINE_K(1, CM_, false);                    \
+    }                                                     \
+  } while (0)
   switch (a.combine) {
-    case 0:
-      if (big) hipLaunchKernelGGL((k_dg_stage<T, NP, 4, 0>), grid, block, 0, s, A, segs);
-      else hipLaunchKernelGGL((k_dg_stage<T, NP, 1, 0>), grid, block, 0, s, A, segs);
-      break;
-    case 1:
-      if (big) hipLaunchKernelGGL((k_dg_stage<T, NP, 4, 1>), grid, block, 0, s, A, segs);
-      else hipLaunchKernelGGL((k_dg_stage<T, NP, 1, 1>), grid, block, 0, s, A, segs);
-      break;
-    case 2:
-      if (big) hipLaunchKernelGGL((k_dg_stage<T, NP, 4, 2>), grid, block, 0, s, A, segs);
-      else hipLaunchKernelGGL((k_dg_stage<T, NP, 1, 2>), grid, block, 0, s, A, segs);
-      break;
+    case 0: DGSW_LINE(0); break;
+    case 1: DGSW_LINE(1); break;
+    case 2: DGSW_LINE(2); break;
     default:
       return hipErrorInvalidValue;
   }
+#undef DGSW_LINE
+#undef DGSW_LINE_K
   return hipGetLastError();
 }
 

@@ -73,6 +73,19 @@ struct Shape {
   // byte alignment of one modal row (NP values) given a 16-byte aligned base
   static constexpr int gcd(int a, int b) { return b == 0 ? a : gcd(b, a % b); }
   static constexpr int ROWALIGN = gcd(16, NP * (int)sizeof(T));
+  // Rows of NP values that are not 16-byte aligned: loaded as rows, a lane at a
+  // time, they cost the address units several cycles a lane (r = 4 FP32 720x360:
+  // busy 83 % of the stage).  With STRIPS the wavefront's data comes and goes in
+  // contiguous runs of whole elements instead: straight into LDS, before the
+  // arrays above take their place, the element west of the segment, the segment,
+  // the element east of it, and the segment's northern and southern neighbours;
+  // the stage's other states and the result value by value.
+  static constexpr bool UNALIGNED = ROWALIGN < 16;
+  static constexpr int EL = 3 * N;                      // values of an element
+  static constexpr int oOwn = EL, oN = (GPW + 2) * EL, oS = oN + GPW * EL, STRIP = oS + GPW * EL;
+  static constexpr int wave(bool strips) {              // LDS values of a wavefront
+    return strips ? cmax((GPW + 1) * SH, STRIP) : (GPW + 1) * SH;
+  }
 };
 
 // Reciprocal and square root from the hardware approximations.  FP64: v_rcp_f64
@@ -139,6 +152,33 @@ __device__ __forceinline__ void store_row(T *p, const T (&r)[NP]) {
 #pragma unroll
   for (int a = 0; a < NP; ++a) pa[a] = r[a];
 }
+
+// `words` 4-byte words (at most MAXW) from p straight into LDS in memory order: a
+// contiguous 256 bytes per load and no registers.
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+template <int MAXW, bool FULL>
+__device__ __forceinline__ void strip_to_lds(const void *p, int words, lds_u32 *dst, int lane) {
+  typedef const __attribute__((address_space(1))) void gptr;
+  typedef __attribute__((address_space(3))) void lptr;
+  const uint32_t *src = static_cast<const uint32_t *>(p);
+#pragma unroll
+  for (int k = 0; k < (MAXW + 63) / 64; ++k) {
+    // 16 loads share their addresses: the instruction's offset moves both sides
+    gptr *b = (gptr *)(src + k / 16 * 1024 + lane);
+    lptr *d = (lptr *)(dst + k / 16 * 1024);
+    if ((FULL && 64 * (k + 1) <= MAXW) || 64 * k + lane < (FULL ? MAXW : words)) {
+      switch (k % 16) {
+#define DGSW_STRIP(K) case K: __builtin_amdgcn_global_load_lds(b, d, 4, 256 * K, 0); break;
+        DGSW_STRIP(0) DGSW_STRIP(1) DGSW_STRIP(2) DGSW_STRIP(3) DGSW_STRIP(4) DGSW_STRIP(5) DGSW_STRIP(6) DGSW_STRIP(7)
+        DGSW_STRIP(8) DGSW_STRIP(9) DGSW_STRIP(10) DGSW_STRIP(11) DGSW_STRIP(12) DGSW_STRIP(13) DGSW_STRIP(14)
+        DGSW_STRIP(15)
+#undef DGSW_STRIP
+      }
+    }
+  }
+}
+// Every load so far, into LDS too, has arrived.
+__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
 // One side of a Rusanov edge: velocity along the edge normal and sqrt(g h).
 // Variable 0 of a trace is h - H; the pressure is g (h^2 - H^2) / 2.
@@ -223,6 +263,56 @@ __device__ __forceinline__ StageArgs<T, NP> layer_args(const StageArgs<T, NP> &A
   return B;
 }
 
+// The stage's result from dq/dt = acc: acc itself, c0 q0 + c1 y = y + c0 (q0 - y) +
+// (c0 + c1 - 1) y with y = q + dt acc, or the general combination.
+template <typename T, typename Args>
+__device__ __forceinline__ T stage_combine(T acc, T qv, T q0v, T xa, T xb, int combine, const Args &A) {
+  if (combine == 2) return q0v + A.dt * acc + (A.c1 * (qv - q0v) + (A.ca * (xa - q0v) + A.cb * (xb - q0v)));
+  if (combine) {
+    const T y = qv + A.dt * acc;
+    return y + A.c0 * (q0v - y) + A.ce * y;
+  }
+  return acc;
+}
+
+// The epilogue in strips: nv <= MAXV values from `base` on, their dq/dt in sh,
+// value 64 k + lane by value.  FULL: nv == MAXV.
+template <typename T, int NP, int MAXV, bool FULL>
+__device__ __forceinline__ void strip_epilogue(const StageArgs<T, NP> &A, int combine, bool use_q0, size_t base,
+                                               int nv, const T *sh, int lane) {
+  constexpr int VL = (MAXV + 63) / 64;
+  const T *__restrict__ q = A.q + base, *__restrict__ f = A.forcing ? A.forcing + base : nullptr;
+  const T *q0 = A.q0 + base, *qa = A.qa + base, *qb = A.qb + base;
+  T *out = A.out + base;
+  T qv[VL], q0v[VL], xa[VL], xb[VL];
+  // lanes past the end read the last value
+  auto at = [&](int k) { return (FULL && 64 * (k + 1) <= MAXV) || 64 * k + lane < nv ? 64 * k + lane : nv - 1; };
+#pragma unroll
+  for (int k = 0; k < VL; ++k) {
+    qv[k] = combine ? q[at(k)] : T(0);
+    q0v[k] = xa[k] = xb[k] = T(0);
+  }
+  if (use_q0) {
+#pragma unroll
+    for (int k = 0; k < VL; ++k) q0v[k] = q0[at(k)];
+  }
+  if (combine == 2 && A.qa) {
+#pragma unroll
+    for (int k = 0; k < VL; ++k) xa[k] = qa[at(k)];
+  }
+  if (combine == 2 && A.qb) {
+#pragma unroll
+    for (int k = 0; k < VL; ++k) xb[k] = qb[at(k)];
+  }
+#pragma unroll
+  for (int k = 0; k < VL; ++k) {
+    T acc = sh[at(k)];
+    if (f) acc += f[at(k)];
+    const T r = stage_combine<T>(acc, qv[k], q0v[k], xa[k], xb[k], combine, A);
+    if ((FULL && 64 * (k + 1) <= MAXV) || 64 * k + lane < nv) out[64 * k + lane] = r;
+  }
+}
+
 // One wavefront's share of a stage: GPW elements of one latitude row
 // (segment `seg` of row j), so the row's tables are wave-uniform (scalar
 // loads) and the pole tests are uniform branches.  tab and sh are this
@@ -232,7 +322,7 @@ __device__ __forceinline__ StageArgs<T, NP> layer_args(const StageArgs<T, NP> &A
 // take 0 or 1 from A.combine (the ensemble kernels).
 constexpr int CM_RUNTIME = 3;
 
-template <typename T, int NP, int CM>
+template <typename T, int NP, int CM, bool STRIPS>
 __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int j, const int seg,
                                            const int lane, T *tab, T *sh) {
   using S_ = Shape<T, NP>;
@@ -241,8 +331,15 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   const T *q0 = A.q0;
   T *out = A.out;
   const T *__restrict__ forcing = A.forcing;
-  const GlobTab<T, NP> *__restrict__ gt = A.gt;
-  const RowTab<T, NP> *__restrict__ rows = A.rows;
+  // the tables, never written while a stage runs; with strips and in FP32 in the
+  // constant address space, whose uniform loads are scalar ones also behind the
+  // loads into LDS, and may be moved freely (r = 3 FP32 720x360 38.2 -> 35.7 us)
+  constexpr bool CAS = STRIPS || sizeof(T) == 4;
+  using GT_ = const GlobTab<T, NP>;
+  using RT_ = const RowTab<T, NP>;
+  using glob_p = typename std::conditional<CAS, __attribute__((address_space(4))) GT_ *, GT_ *>::type;
+  using row_p = typename std::conditional<CAS, __attribute__((address_space(4))) RT_ *, RT_ *>::type;
+  const glob_p gt = (glob_p)A.gt;
   const int n_lon = A.n_lon, n_lat = A.n_lat;
   const int combine = CM == CM_RUNTIME ? (A.combine != 0 ? 1 : 0) : CM;
   const T c0 = A.c0, c1 = A.c1, dt = A.dt;
@@ -254,7 +351,7 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   const int i = i_raw < n_lon ? i_raw : n_lon - 1;   // tail lanes work on a valid element
   const int e = j * n_lon + i;
   T *S = sh + g * SH;
-  const RowTab<T, NP> *rt = rows + j;
+  const row_p rt = (row_p)(A.rows + j);
   const bool periodic = A.periodic_y != 0;
   const bool hasN = periodic || j < n_lat - 1, hasS = periodic || j > 0;
   // north / south neighbours (rows wrap on the plane)
@@ -265,48 +362,90 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   const T alpha = gt->alpha;
 
   // ---- every global load of the stage, issued up front
+  constexpr int EL = S_::EL;
+  const int i0 = seg * GPW, cnt = n_lon - i0 < GPW ? n_lon - i0 : GPW;
   const size_t row_off = (size_t)t * NP;
   const size_t base = (size_t)e * 3 * N + row_off;
-  const int eE = (i + 1 == n_lon) ? e + 1 - n_lon : e + 1;
-  const int eW = (i == 0) ? e - 1 + n_lon : e - 1;
   T qr[3][NP], xE[3][NP], xW[3][NP], xN[3][NP], xS[3][NP];
-#pragma unroll
-  for (int v = 0; v < 3; ++v) {
-    load_row<T, NP>(q + base + v * N, qr[v]);
-    load_row<T, NP>(q + (size_t)eE * 3 * N + row_off + v * N, xE[v]);   // row b = t
-    load_row<T, NP>(q + (size_t)eW * 3 * N + row_off + v * N, xW[v]);
-  }
-  if (hasN) {
-    const T *c = q + (size_t)eN * 3 * N + t;                             // column a = t
-#pragma unroll
-    for (int v = 0; v < 3; ++v)
-#pragma unroll
-      for (int k = 0; k < NP; ++k) xN[v][k] = c[v * N + k * NP];
+  if constexpr (STRIPS) {
+    constexpr int WPV = sizeof(T) / 4;                       // 4-byte words per value
+    const T *qrow = q + (size_t)(j * n_lon) * EL, *own = qrow + (size_t)i0 * EL;
+    const int iW = i0 == 0 ? n_lon - 1 : i0 - 1, iE = i0 + cnt == n_lon ? 0 : i0 + cnt;
+    // across a pole (no flux there) the segment stands in for its neighbour
+    const int jN = j < n_lat - 1 ? j + 1 : (periodic ? 0 : j), jS = j > 0 ? j - 1 : (periodic ? n_lat - 1 : j);
+    const T *nrow = q + (size_t)(jN * n_lon + i0) * EL, *srow = q + (size_t)(jS * n_lon + i0) * EL;
+    lds_u32 *w = (lds_u32 *)sh;
+    strip_to_lds<EL * WPV, true>(qrow + (size_t)iW * EL, 0, w, lane);
+    strip_to_lds<EL * WPV, true>(qrow + (size_t)iE * EL, 0, w + (S_::oOwn + cnt * EL) * WPV, lane);
+    if (cnt == GPW) {
+      strip_to_lds<GPW * EL * WPV, true>(own, 0, w + S_::oOwn * WPV, lane);
+      strip_to_lds<GPW * EL * WPV, true>(nrow, 0, w + S_::oN * WPV, lane);
+      strip_to_lds<GPW * EL * WPV, true>(srow, 0, w + S_::oS * WPV, lane);
+    } else {
+      strip_to_lds<GPW * EL * WPV, false>(own, cnt * EL * WPV, w + S_::oOwn * WPV, lane);
+      strip_to_lds<GPW * EL * WPV, false>(nrow, cnt * EL * WPV, w + S_::oN * WPV, lane);
+      strip_to_lds<GPW * EL * WPV, false>(srow, cnt * EL * WPV, w + S_::oS * WPV, lane);
+    }
   } else {
+    const int eE = (i + 1 == n_lon) ? e + 1 - n_lon : e + 1;
+    const int eW = (i == 0) ? e - 1 + n_lon : e - 1;
 #pragma unroll
-    for (int v = 0; v < 3; ++v)
+    for (int v = 0; v < 3; ++v) {
+      load_row<T, NP>(q + base + v * N, qr[v]);
+      load_row<T, NP>(q + (size_t)eE * 3 * N + row_off + v * N, xE[v]);   // row b = t
+      load_row<T, NP>(q + (size_t)eW * 3 * N + row_off + v * N, xW[v]);
+    }
+    if (hasN) {
+      const T *c = q + (size_t)eN * 3 * N + t;                             // column a = t
 #pragma unroll
-      for (int k = 0; k < NP; ++k) xN[v][k] = T(0);
-  }
-  if (hasS) {
-    const T *c = q + (size_t)eS * 3 * N + t;
+      for (int v = 0; v < 3; ++v)
 #pragma unroll
-    for (int v = 0; v < 3; ++v)
+        for (int k = 0; k < NP; ++k) xN[v][k] = c[v * N + k * NP];
+    } else {
 #pragma unroll
-      for (int k = 0; k < NP; ++k) xS[v][k] = c[v * N + k * NP];
-  } else {
+      for (int v = 0; v < 3; ++v)
 #pragma unroll
-    for (int v = 0; v < 3; ++v)
+        for (int k = 0; k < NP; ++k) xN[v][k] = T(0);
+    }
+    if (hasS) {
+      const T *c = q + (size_t)eS * 3 * N + t;
 #pragma unroll
-      for (int k = 0; k < NP; ++k) xS[v][k] = T(0);
+      for (int v = 0; v < 3; ++v)
+#pragma unroll
+        for (int k = 0; k < NP; ++k) xS[v][k] = c[v * N + k * NP];
+    } else {
+#pragma unroll
+      for (int v = 0; v < 3; ++v)
+#pragma unroll
+        for (int k = 0; k < NP; ++k) xS[v][k] = T(0);
+    }
   }
   {
     // one round of 64 lanes up to r = 4 (a single wait, which the state
     // loads need anyway); the registers of a two-phase copy would push the
     // FP64 r >= 4 kernels into scratch
-    const T *gB = &gt->B[0][0], *gw = &gt->w[0], *rBM = &rt->BM[0][0];
+    const T *gB = &A.gt->B[0][0], *gw = &A.gt->w[0], *rBM = &A.rows[j].BM[0][0];
     for (int k = lane; k < S_::TBU; k += 64)
       tab[k] = k < NP * NP ? gB[k] : (k < NP * NP + NP ? gw[k - NP * NP] : rBM[k - NP * NP - NP]);
+  }
+  if constexpr (STRIPS) {
+    loads_done();
+    wave_sync();
+    // row b = t of the element and of its longitude neighbours, column a = t of
+    // the latitude ones (lanes without an element read the segment's last)
+    const int ge = i - i0;
+    const T *o = sh + S_::oOwn + ge * EL, *oN = sh + S_::oN + ge * EL, *oS = sh + S_::oS + ge * EL;
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        qr[v][k] = o[v * N + t * NP + k];
+        xE[v][k] = o[EL + v * N + t * NP + k];
+        xW[v][k] = o[-EL + v * N + t * NP + k];
+        xN[v][k] = oN[v * N + k * NP + t];
+        xS[v][k] = oS[v * N + k * NP + t];
+      }
+    wave_sync();
   }
 
   // ---- xi pass: A[v][p][b=t] and the xi = +1/-1 rows; neighbour partial sums
@@ -451,12 +590,12 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   }
   wave_sync();
 
-  // ---- the epilogue's operands, loaded late to keep registers free: q (again,
-  // from cache), q^n and the forcing
+  // ---- the epilogue's operands (rows), loaded late to keep registers free: q
+  // (again, from cache), q^n and the forcing
   const bool use_q0 = combine == 2 || (combine == 1 && c0 != T(0));
-  T q0r[3][NP], fr[3][NP];
+  T q0r[3][NP], fr[3][NP], res[3][NP];
 #pragma unroll
-  for (int v = 0; v < 3; ++v) {
+  for (int v = 0; v < 3 && !STRIPS; ++v) {
     if (combine) load_row<T, NP>(q + base + v * N, qr[v]);
     if (use_q0) {
       load_row<T, NP>(q0 + base + v * N, q0r[v]);
@@ -487,19 +626,11 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
       XE += S[6 * NP * NP + (v * 2 + 0) * NP + p] * bmt[p];
       XW += S[6 * NP * NP + (v * 2 + 1) * NP + p] * bmt[p];
     }
-    // general combination (combine == 2, classical RK4): its two extra
-    // operands, loaded one variable at a time
-    T xa[NP], xb[NP];
-#pragma unroll
-    for (int a = 0; a < NP; ++a) xa[a] = xb[a] = T(0);
-    if (combine == 2 && A.qa) load_row<T, NP>(A.qa + base + v * N, xa);
-    if (combine == 2 && A.qb) load_row<T, NP>(A.qb + base + v * N, xb);
-    T res[NP];
     const T cXE = cF * XE, cXW = cF * XW;
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
       // the forcing, then chained FMAs (a sum of products first costs a third instruction)
-      T acc = fr[v][a];
+      T acc = STRIPS ? T(0) : fr[v][a];
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
         acc += gt->D[p][a] * zd[p];
@@ -507,18 +638,36 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
       }
       acc -= gt->Pp[a] * cXE;
       acc += gt->Pm[a] * cXW;
-      if (combine == 2) {
-        const T b0 = q0r[v][a];
-        res[a] = b0 + dt * acc + (c1 * (qr[v][a] - b0) + (A.ca * (xa[a] - b0) + A.cb * (xb[a] - b0)));
-      } else if (combine) {
-        // c0 q0 + c1 y = y + c0 (q0 - y) + (c0 + c1 - 1) y, y = q + dt L
-        const T y = qr[v][a] + dt * acc;
-        res[a] = y + c0 * (q0r[v][a] - y) + A.ce * y;
-      } else {
-        res[a] = acc;
-      }
+      res[v][a] = acc;
     }
-    if (active) store_row<T, NP>(out + base + v * N, res);
+    if constexpr (!STRIPS) {
+      // general combination (combine == 2, classical RK4): its two extra
+      // operands, loaded one variable at a time
+      T xa[NP], xb[NP];
+#pragma unroll
+      for (int a = 0; a < NP; ++a) xa[a] = xb[a] = T(0);
+      if (combine == 2 && A.qa) load_row<T, NP>(A.qa + base + v * N, xa);
+      if (combine == 2 && A.qb) load_row<T, NP>(A.qb + base + v * N, xb);
+#pragma unroll
+      for (int a = 0; a < NP; ++a)
+        res[v][a] = stage_combine<T>(res[v][a], qr[v][a], q0r[v][a], xa[a], xb[a], combine, A);
+      if (active) store_row<T, NP>(out + base + v * N, res[v]);
+    }
+  }
+  if constexpr (STRIPS) {
+    wave_sync();
+    if (active) {
+      T *o = sh + g * EL + t * NP;
+#pragma unroll
+      for (int v = 0; v < 3; ++v)
+#pragma unroll
+        for (int a = 0; a < NP; ++a) o[v * N + a] = res[v][a];
+    }
+    wave_sync();
+    const int nv = cnt * EL;
+    const size_t sbase = (size_t)(j * n_lon + i0) * EL;
+    if (cnt == GPW) strip_epilogue<T, NP, GPW * EL, true>(A, combine, use_q0, sbase, nv, sh, lane);
+    else strip_epilogue<T, NP, GPW * EL, false>(A, combine, use_q0, sbase, nv, sh, lane);
   }
 }
 

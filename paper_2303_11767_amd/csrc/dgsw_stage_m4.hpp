@@ -136,12 +136,6 @@ struct M4Group {
   long long off;
 };
 
-// Groups of a mesh: every four elements across row ends, or (rows of fewer
-// than four) one per row.
-__host__ __device__ __forceinline__ int m4_groups(int n_lon, int n_lat) {
-  return n_lon >= kM4Elems ? (int)(((long long)n_lon * n_lat + kM4Elems - 1) / kM4Elems) : n_lat;
-}
-
 // Group k of a layer at offset off.
 __device__ __forceinline__ M4Group m4_group(int n_lon, int n_lat, int k, long long off) {
   const bool wide = n_lon >= kM4Elems;
@@ -422,18 +416,33 @@ __device__ __forceinline__ void m4_have_read() {
   asm volatile("" ::: "memory");
 }
 
-// One group by itself.
-template <int CM>
-__device__ __forceinline__ void m4_one(const StageArgs<double, 4> &A, const M4Group &g, int lane, lds_double *sh) {
-  const bool use_q0 = CM == 1 && A.c0 != 0.0;
-  m4_fetch(A, g, use_q0, lane, sh);
+// `count` groups, group(0) .. group(count - 1), one after the other: the next
+// one's data is fetched while the present one is worked on.
+template <int CM, bool MORE, typename Group>
+__device__ __forceinline__ void m4_run(const StageArgs<double, 4> &A, int count, Group group, int lane,
+                                       lds_double *sh) {
+  const bool use_q0 = CM == 2 || (CM == 1 && A.c0 != 0.0);
   const M4Tab t = m4_tables(A.gt, lane);
+  M4Group g = group(0);
+  m4_fetch(A, g, use_q0, lane, sh);
   m4_fetched();
-  M4Data d = m4_read(A, g, use_q0, lane, sh);
-  m4_compute<CM>(A, t, d, M4More{}, lane, sh);
-  wave_sync();
-  m4_store(A, g, lane, sh);
-  m4_have_read();   // before the wavefront's next group arrives
+  for (int n = 1;; ++n) {
+    M4Data d = m4_read(A, g, use_q0, lane, sh);
+    const M4More o = m4_more<CM, MORE>(A, g, lane);
+    m4_have_read();
+    M4Group next = g;
+    if (n < count) {
+      next = group(n);
+      m4_fetch(A, next, use_q0, lane, sh);
+    }
+    m4_compute<CM>(A, t, d, o, lane, sh);
+    wave_sync();
+    // the next group's data before the stores are queued behind them
+    if (n < count) m4_fetched();
+    m4_store(A, g, lane, sh);
+    if (n >= count) break;
+    g = next;
+  }
 }
 
 }  // namespace dgsw
