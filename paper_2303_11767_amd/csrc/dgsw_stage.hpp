@@ -55,6 +55,18 @@
 namespace dgsw {
 
 
+// LDS strides of an element's arrays (values), by r + 1: the paddings with the
+// fewest bank conflicts over the stage's accesses among those up to 28 values
+// (r = 1, whose unpadded stride makes most of its LDS accesses wait eight times:
+// stage times before and after at 720x360, FP64 half 29.9 / 23.5 us and line 36.8 /
+// 27.4, FP32 18.0 / 14.6 and 19.2 / 13.5; other orders within 2 %).
+template <typename T>
+constexpr int lds_stride(int np, int used, bool half) {
+  constexpr int line32[9] = {0, 21, 50, 81, 120, 185, 266, 347, 436}, line64[9] = {0, 21, 50, 81, 122, 185, 260, 340, 434};
+  constexpr int half32[9] = {0, 22, 52, 101, 152, 217, 298, 392, 492}, half64[9] = {0, 22, 52, 92, 120, 217, 264, 392, 434};
+  return np > 8 ? used : (sizeof(T) == 4 ? (half ? half32[np] : line32[np]) : (half ? half64[np] : line64[np]));
+}
+
 template <typename T, int NP>
 struct Shape {
   static constexpr int N = NP * NP;
@@ -64,7 +76,14 @@ struct Shape {
   //   A/B: the xi-pass rows (n+2 per variable) and the neighbour partial sums
   //   C/D: the second transpose (two n x n per variable) and the E/W edge fluxes
   static constexpr int NB = 3 * (NP + 2) * NP;
-  static constexpr int SH = cmax(NB + 12 * NP, 6 * NP * NP + 6 * NP);
+  static constexpr int USED = cmax(NB + 12 * NP, 6 * NP * NP + 6 * NP);
+  // the elements' stride, padded so that the lanes of a half wavefront (element
+  // g, line t) spread over the banks in the three ways the arrays are read and
+  // written (values g SH + t, g SH + t NP + const, g SH + const), and rows stay
+  // aligned for wide reads: at r = 1 the unpadded stride puts 16 elements on two
+  // bank offsets
+  static constexpr int SH = lds_stride<T>(NP, USED, false);
+  static_assert(SH >= USED, "element stride");
   // tables read with a lane-dependent index, copied to LDS per wavefront:
   // P~(xi_p) [p][a], weights, and the row's BM [s][b] (TBU values), the
   // region rounded up to whole 64-lane rounds of the copy
@@ -700,7 +719,9 @@ struct ShapeH2 {
   // [XQ][NP][NP] at a time, use the region of the volume outputs first (both
   // are read before those are written).
   static constexpr int oFX = 6 * NP * NP, oGY = SPLIT ? 0 : oFX + 6 * NP, XQ = 4;
-  static constexpr int SH = cmax(NB + 12 * NP, oFX + (SPLIT ? 6 : 12) * NP);
+  static constexpr int USED = cmax(NB + 12 * NP, oFX + (SPLIT ? 6 : 12) * NP);
+  static constexpr int SH = lds_stride<T>(NP, USED, true);   // padded as Shape's
+  static_assert(SH >= USED, "element stride");
   static constexpr int SLOTS = GPW + (SPARE ? 1 : 0);
   // LDS copy of the tables: the GlobTab prefix (B, D, Pp, Pm, w), then the
   // whole RowTab of the wavefront's first row and of the row after it (a
