@@ -47,7 +47,10 @@ __device__ __forceinline__ float gauss(float z) { return __builtin_amdgcn_exp2f(
 
 __device__ __forceinline__ float gelu_f(float z) {
   const float az = fabsf(z);
-  return fmaf(-az * gelu_as::half_poly(az), gelu_as::gauss(z), fmaxf(z, 0.0f));
+  // max(z, 0) on the bits: fmaxf() also quiets its operand, one more
+  // instruction of 15 (a NaN reaches the sum through az)
+  const float zp = __int_as_float(max(__float_as_int(z), 0));
+  return fmaf(-az * gelu_as::half_poly(az), gelu_as::gauss(z), zp);
 }
 // GELU(z) and, in place of z, GELU'(z): one reciprocal and one exponential for both.
 __device__ __forceinline__ float gelu_and_grad(float &z) {
@@ -70,9 +73,15 @@ __device__ __forceinline__ float gelu_and_grad(float &z) {
 // global memory.  Each product is computed transposed, out^T = W in^T: the
 // weights are the MFMA A operand (row = unit, 8 consecutive k per lane) and
 // the LDS rows the B operand, so every lane ends with 4 consecutive units of
-// one row and writes them as one 8-byte LDS store.  Same rounding points as
-// the unfused path: BF16 inputs, weights and hidden activations, FP32
-// accumulation, bias and GELU in FP32.
+// one row and writes them as one 8-byte LDS store.  Rounding points: BF16
+// inputs, weights and hidden activations, FP32 accumulation, bias and GELU in
+// FP32.  Bound by the vector unit (GELU: 14 instructions per unit and row,
+// 45 k of the 72 k cycles; the matrix cores are busy for 13 k and the weights'
+// first load takes about 10 k).  Inputs have a buffer of their own, so a tile
+// has three barriers and the next tile's operands are fetched meanwhile: with
+// the operands fetched at the tile's start and rows padded instead of permuted
+// 40.0 us for 64 800 rows, now 36.8; weights streamed from L2 for two
+// workgroups per CU took 38.8.
 constexpr int kRows = 64;                 // rows per tile
 constexpr int kMlpGrid = 256;             // persistent workgroups: one per MI355X compute unit
 template <typename T>
@@ -90,25 +99,34 @@ constexpr int kLd = kHidden + 8;          // LDS row stride in BF16 (+16 B: no b
 constexpr int kYs = kRows + 4;            // stride of the network outputs' unit columns in LDS
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
+// Offset in BF16 of the 16-byte chunk c of an LDS row of whole 256-byte
+// multiples: chunks are permuted within a row by the row's index, so that the
+// rows a wavefront reads or writes at one column lie in different banks
+// whatever 16 lanes the unit takes together.  (Rows padded by 16 bytes
+// instead: half of the cycles of the reads were bank conflicts.)
+__device__ __forceinline__ int swz(int c, int row) { return (c ^ (row & 15)) * 8; }
+
 // One hidden layer for the 64 rows of a tile: wavefront wv computes units
 // [32 wv, 32 wv + 32) of out = gelu(in W^T + b), K inputs per row, from the
 // weight fragments w[ks][nt] it holds.
 template <int K>
-__device__ __forceinline__ void fused_hidden(const bf16x8 (&w)[K / 32][2], const f32x4 (&bv)[2], const __bf16 *in,
+__device__ __forceinline__ void fused_hidden(const bf16x8 (&w)[K / 32][2], const float *bias, const __bf16 *in,
                                              __bf16 *out, int wv, int lane) {
   constexpr int NT = 2, MT = kRows / 16, KS = K / 32;
-  const int r = lane & 15, kq = (lane >> 4) * 8;
+  const int r = lane & 15, kc = lane >> 4;
   f32x4 acc[NT][MT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
+  for (int nt = 0; nt < NT; ++nt) {
+    const f32x4 bv = *reinterpret_cast<const f32x4 *>(bias + 32 * wv + 16 * nt + kc * 4);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = bv[nt];   // the bias, then the products
+    for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = bv;   // the bias, then the products
+  }
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     bf16x8 b[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-      b[mt] = *reinterpret_cast<const bf16x8 *>(in + (16 * mt + r) * kLd + 32 * ks + kq);
+      b[mt] = *reinterpret_cast<const bf16x8 *>(in + (16 * mt + r) * K + swz(4 * ks + kc, r));
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -117,13 +135,13 @@ __device__ __forceinline__ void fused_hidden(const bf16x8 (&w)[K / 32][2], const
   }
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    const int n0 = 32 * wv + 16 * nt + (lane >> 4) * 4;
+    const int col = swz(4 * wv + 2 * nt + (kc >> 1), r) + 4 * (kc & 1);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       bf16x4 h;
 #pragma unroll
       for (int i = 0; i < 4; ++i) h[i] = (__bf16)gelu_f(acc[nt][mt][i]);
-      *reinterpret_cast<bf16x4 *>(out + (16 * mt + r) * kLd + n0) = h;
+      *reinterpret_cast<bf16x4 *>(out + (16 * mt + r) * kHidden + col) = h;
     }
   }
 }
@@ -132,14 +150,13 @@ __device__ __forceinline__ void fused_hidden(const bf16x8 (&w)[K / 32][2], const
 // the fragment order Wf (one contiguous kilobyte per load), and the matching
 // biases.
 template <int K>
-__device__ __forceinline__ void load_hidden(const __bf16 *__restrict__ Wf, const float *__restrict__ bias, int wv,
-                                            int lane, bf16x8 (&w)[K / 32][2], f32x4 (&bv)[2]) {
+__device__ __forceinline__ void load_hidden(const __bf16 *__restrict__ Wf, int wv,
+                                            int lane, bf16x8 (&w)[K / 32][2]) {
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt) {
     const __bf16 *blk = Wf + (size_t)(2 * wv + nt) * (K / 32) * 512 + lane * 8;
 #pragma unroll
     for (int ks = 0; ks < K / 32; ++ks) w[ks][nt] = *reinterpret_cast<const bf16x8 *>(blk + 512 * ks);
-    bv[nt] = *reinterpret_cast<const f32x4 *>(bias + 32 * wv + 16 * nt + (lane >> 4) * 4);
   }
 }
 
@@ -179,7 +196,7 @@ __device__ __forceinline__ bool correction_row(const float *y, const float *L1e,
 // partial[blockIdx.x] and the fallback count; else the network on rows of
 // X[rows][108], output Y[rows][32].  Tiles blockIdx.x, blockIdx.x + gridDim.x, ..
 template <typename T, bool FROM_Q>
-__global__ __launch_bounds__(64 * kWaves) void k_mlp_fused(const T *__restrict__ q, int n_lon, int n_lat,
+__global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(64 * kWaves) void k_mlp_fused(const T *__restrict__ q, int n_lon, int n_lat,
                                                           const float *__restrict__ fmean,
                                                           const float *__restrict__ fistd,
                                                           const float *__restrict__ X, int rows,
@@ -189,9 +206,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp_fused(const T *__restrict__
                                                           const float *__restrict__ b1, const float *__restrict__ b2,
                                                           const float *__restrict__ b3p, float *__restrict__ Y,
                                                           MlpCorrection<T> cor) {
-  __shared__ __attribute__((aligned(16))) __bf16 buf0[kRows * kLd];
-  __shared__ __attribute__((aligned(16))) __bf16 buf1[kRows * kLd];
-  __shared__ __attribute__((aligned(16))) __bf16 st_w3[kOutPad * kLd];
+  __shared__ __attribute__((aligned(16))) __bf16 bufx[kRows * kInPad];    // inputs
+  __shared__ __attribute__((aligned(16))) __bf16 buf1[kRows * kHidden];   // first and second hidden layer
+  __shared__ __attribute__((aligned(16))) __bf16 buf2[kRows * kHidden];
+  __shared__ __attribute__((aligned(16))) __bf16 st_w3[kOutPad * kHidden];
+  __shared__ __attribute__((aligned(16))) float st_b1[kHidden], st_b2[kHidden];
+  __shared__ float ys[FROM_Q ? kOutPad * kYs : 1];                        // outputs, for the correction
   // the correction's operands of the tile's rows (FROM_Q): the r = 1
   // right-hand side, the output mean and spread of the row's latitude (value
   // k of row i at k kRows + i: the lane-per-row reads hit distinct banks), the
@@ -200,50 +220,49 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp_fused(const T *__restrict__
   __shared__ double st_mw[FROM_Q ? kRows : 1];
   // the feature standardisation (FROM_Q), once per workgroup
   __shared__ float st_fm[FROM_Q ? kFeatures : 1], st_fi[FROM_Q ? kFeatures : 1];
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, kq = (lane >> 4) * 8;
-  // the output layer's weights in LDS (rows padded like the activations):
+  // the output layer's weights in LDS (chunks permuted like the activations):
   // registers held for 8 products per tile would push the kernel into scratch
   for (int c = tid; c < kOutPad * kHidden / 8; c += 64 * kWaves) {
     const int u = c / (kHidden / 8), k8 = c - u * (kHidden / 8);
-    *reinterpret_cast<bf16x8 *>(st_w3 + u * kLd + 8 * k8) =
+    *reinterpret_cast<bf16x8 *>(st_w3 + u * kHidden + swz(k8, u)) =
         *reinterpret_cast<const bf16x8 *>(W3t + (size_t)u * kHidden + 8 * k8);
   }
   // the hidden layers' weights in registers, requested after the LDS tables
   // (loads complete in order: the tables' stores wait only for their own
   // loads, and these arrive while the first tile's inputs are fetched)
   bf16x8 w1[kInPad / 32][2], w2[kHidden / 32][2];
-  f32x4 bv1[2], bv2[2];
   // output layer: wavefront wv takes rows [16 (wv / 2), +16) and units [16 (wv % 2), +16)
   const int mt = wv >> 1, nt = wv & 1;
-  const int n0 = 16 * nt + (lane >> 4) * 4;
-  const f32x4 bv3 = *reinterpret_cast<const f32x4 *>(b3p + n0);
+  const f32x4 bv3 = *reinterpret_cast<const f32x4 *>(b3p + 16 * nt + (lane >> 4) * 4);
   // zero padding of the inputs beyond the 108 features (never overwritten)
-  for (int idx = tid; idx < kRows * (kInPad - kFeatures); idx += 64 * kWaves) {
-    const int rr = idx / (kInPad - kFeatures);
-    buf0[rr * kLd + kFeatures + (idx - rr * (kInPad - kFeatures))] = (__bf16)0.f;
+  for (int idx = tid; idx < kRows * (kInPad - kFeatures) / 4; idx += 64 * kWaves) {
+    const int rr = idx / ((kInPad - kFeatures) / 4), k = kFeatures + 4 * (idx - rr * ((kInPad - kFeatures) / 4));
+    *reinterpret_cast<bf16x4 *>(bufx + rr * kInPad + swz(k >> 3, rr) + (k & 4)) = bf16x4{};
   }
+  if (tid < kHidden)
+    st_b1[tid] = b1[tid];
+  else
+    st_b2[tid - kHidden] = b2[tid - kHidden];
   if constexpr (FROM_Q) {
     for (int k = tid; k < kFeatures; k += 64 * kWaves) {
       st_fm[k] = fmean[k];
       st_fi[k] = fistd[k];
     }
   }
-  load_hidden<kInPad>(W1f, b1, wv, lane, w1, bv1);
-  load_hidden<kHidden>(W2f, b2, wv, lane, w2, bv2);
+  load_hidden<kInPad>(W1f, wv, lane, w1);
+  load_hidden<kHidden>(W2f, wv, lane, w2);
   __syncthreads();            // the tables above before their first use
   double mass = 0.0;          // wavefront 0: this workgroup's h-mass of the corrections
   bool any_fell = false;
   unsigned long long fell_count = 0ull;
-  // the 12 values of input task (row rr, stencil neighbour sn), raw, and
-  // their BF16 features in buf0
+  // Input tasks, one per (row, stencil neighbour) of a tile: 12 contiguous
+  // values, and their BF16 features in bufx.
   using In = typename std::conditional<FROM_Q, T, float>::type;
-  int e0 = 0;
-  auto load_task = [&](int task, In (&x)[12]) {
+  auto task_src = [&](int e0, int task) -> const In * {
     const int rr = task / 9, sn = task - rr * 9;
     const int e = e0 + rr < rows ? e0 + rr : rows - 1;
-    const In *src;
     if constexpr (FROM_Q) {
       const int dj = sn / 3 - 1, di = sn % 3 - 1;
       const int j = e / n_lon, i = e - j * n_lon;
@@ -251,88 +270,133 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp_fused(const T *__restrict__
       jj = jj < 0 ? 0 : (jj >= n_lat ? n_lat - 1 : jj);
       int ii = i + di;
       ii = ii < 0 ? ii + n_lon : (ii >= n_lon ? ii - n_lon : ii);
-      src = q + ((size_t)jj * n_lon + ii) * 12;
+      return q + ((size_t)jj * n_lon + ii) * 12;
     } else {
-      src = X + (size_t)e * kFeatures + sn * 12;
+      return X + (size_t)e * kFeatures + sn * 12;
     }
-#pragma unroll
-    for (int vm = 0; vm < 12; ++vm) x[vm] = src[vm];
   };
-  auto store_task = [&](int task, const In (&raw)[12]) {
+  auto store_task = [&](int task, auto value) {
     const int rr = task / 9, sn = task - rr * 9;
     float x[12];
 #pragma unroll
-    for (int vm = 0; vm < 12; ++vm) x[vm] = (float)raw[vm];
+    for (int vm = 0; vm < 12; ++vm) x[vm] = value(vm);
     if constexpr (FROM_Q) {
 #pragma unroll
       for (int vm = 0; vm < 12; ++vm) x[vm] = (x[vm] - st_fm[sn * 12 + vm]) * st_fi[sn * 12 + vm];
     }
-    bf16x4 *dst = reinterpret_cast<bf16x4 *>(buf0 + rr * kLd + sn * 12);
 #pragma unroll
     for (int h4 = 0; h4 < 3; ++h4)
-      dst[h4] = bf16x4{(__bf16)x[4 * h4], (__bf16)x[4 * h4 + 1], (__bf16)x[4 * h4 + 2], (__bf16)x[4 * h4 + 3]};
+      *reinterpret_cast<bf16x4 *>(bufx + rr * kInPad + swz((3 * sn + h4) >> 1, rr) + 4 * ((3 * sn + h4) & 1)) =
+          bf16x4{(__bf16)x[4 * h4], (__bf16)x[4 * h4 + 1], (__bf16)x[4 * h4 + 2], (__bf16)x[4 * h4 + 3]};
   };
-  const int ntiles = (rows + kRows - 1) / kRows;
-  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    e0 = tile * kRows;
-    // inputs: one task per (row, stencil neighbour), 12 contiguous values;
-    // the 64 tasks beyond one per lane go to wavefront 0, and the correction's
-    // operands of the tile's rows are staged in LDS by wavefronts 1 .. 3, all
-    // loads issued before any is waited for (one memory round trip per tile)
-    constexpr int kTasks = kRows * 9;
-    static_assert(kTasks > 64 * kWaves && kTasks <= 64 * kWaves + 64, "one extra task per lane of wavefront 0");
-    In raw0[12], raw1[12];
-    load_task(tid, raw0);
-    if (wv == 0) load_task(tid + 64 * kWaves, raw1);
+  // The operands of a tile that come from memory, requested before its first
+  // layer and stored after a later one: raw, the next tile's input tasks;
+  // half, per lane two pieces of 6 In each: wavefront kExtra the tasks beyond
+  // one per lane, wavefronts 1 .. 3 the correction's operands of this tile's
+  // rows (the right-hand side, then the output mean and spread, 12 floats each:
+  // with FP64 one piece, with FP32 two); wavefront 5 the h-mass weight.
+  constexpr int kTasks = kRows * 9, kExtra = 4;
+  static_assert(kTasks > 64 * kWaves && kTasks <= 64 * kWaves + 64, "one extra task per lane of one wavefront");
+  constexpr bool kWide = sizeof(In) == 8;
+  constexpr int kWords = 3 * sizeof(In);            // of the 12 values, in 32 bits
+  In raw[12];
+  unsigned half[kWords];
+  double mw = 0.0;
+  auto load_tile = [&](int e0, int e0n) {
+    const In *src = task_src(e0n, tid);
+#pragma unroll
+    for (int vm = 0; vm < 12; ++vm) raw[vm] = src[vm];
+    if (FROM_Q ? (wv >= 1 && wv <= kExtra) : wv == kExtra) {
+      const In *p0, *p1;
+      if (wv == kExtra) {
+        p0 = task_src(e0n, lane + 64 * kWaves);
+        p1 = p0 + 6;
+      } else if constexpr (FROM_Q) {
+        const int e = e0 + lane < rows ? e0 + lane : rows - 1;
+        const int j = e / n_lon;
+        if (wv == 1) {
+          p0 = cor.L1 + (size_t)e * 12;
+          p1 = p0 + 6;
+        } else {
+          const float *f0 = (wv == 2 ? cor.omean : cor.ostd) + j * 12;
+          p0 = reinterpret_cast<const In *>(f0);
+          p1 = kWide ? reinterpret_cast<const In *>(cor.ostd + j * 12) : p0 + 6;
+        }
+      }
+      const unsigned *u0 = reinterpret_cast<const unsigned *>(p0), *u1 = reinterpret_cast<const unsigned *>(p1);
+#pragma unroll
+      for (int k = 0; k < kWords / 2; ++k) half[k] = u0[k];
+#pragma unroll
+      for (int k = 0; k < kWords / 2; ++k) half[kWords / 2 + k] = u1[k];
+    }
     if constexpr (FROM_Q) {
-      const int e = e0 + lane < rows ? e0 + lane : rows - 1;
-      const int j = e / n_lon;
-      if (wv == 1) {
-        const T *src = cor.L1 + (size_t)e * 12;
-        T l1[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) l1[k] = src[k];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) st_l1[k * kRows + lane] = (float)l1[k];
-      } else if (wv == 2) {
-        float om[12], os[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) {
-          om[k] = cor.omean[j * 12 + k];
-          os[k] = cor.ostd[j * 12 + k];
-        }
-#pragma unroll
-        for (int k = 0; k < 12; ++k) {
-          st_om[k * kRows + lane] = om[k];
-          st_os[k * kRows + lane] = os[k];
-        }
-      } else if (wv == 3) {
-        st_mw[lane] = cor.mass_w[j * 2 + 1];
+      if (wv == 5) {
+        const int e = e0 + lane < rows ? e0 + lane : rows - 1;
+        mw = cor.mass_w[e / n_lon * 2 + 1];
       }
     }
-    store_task(tid, raw0);
-    if (wv == 0) store_task(tid + 64 * kWaves, raw1);
-    __syncthreads();
-    fused_hidden<kInPad>(w1, bv1, buf0, buf1, wv, lane);
-    __syncthreads();
-    fused_hidden<kHidden>(w2, bv2, buf1, buf0, wv, lane);
+  };
+  auto half_value = [&](int k) -> float {
+    if constexpr (kWide)
+      return (float)__hiloint2double((int)half[2 * k + 1], (int)half[2 * k]);
+    else
+      return __uint_as_float(half[k]);
+  };
+  auto store_operands = [&]() {
+    if (wv == 1) {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) st_l1[k * kRows + lane] = half_value(k);
+    } else if (wv == 2 || (!kWide && wv == 3)) {
+      float *dst = (wv == 2 ? st_om : st_os) + lane;
+#pragma unroll
+      for (int k = 0; k < 12; ++k) dst[k * kRows] = __uint_as_float(half[k]);
+      if constexpr (kWide) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) st_os[k * kRows + lane] = __uint_as_float(half[12 + k]);
+      }
+    } else if (wv == 5) {
+      st_mw[lane] = mw;
+    }
+  };
+  auto store_inputs = [&]() {
+    store_task(tid, [&](int k) { return (float)raw[k]; });
+    if (wv == kExtra) store_task(lane + 64 * kWaves, half_value);
+  };
+  const int ntiles = (rows + kRows - 1) / kRows;
+  load_tile(blockIdx.x * kRows, blockIdx.x * kRows);
+  store_inputs();
+  __syncthreads();
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int e0 = tile * kRows;
+    // opaque to the compiler: offsets that depend on the lane alone are formed
+    // again for each tile, not held in registers beside the weights
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    const int r = lane & 15, kc = lane >> 4, n0 = 16 * nt + 4 * kc;
+    load_tile(e0, tile + (int)gridDim.x < ntiles ? (tile + (int)gridDim.x) * kRows : e0);   // (after the last: not used)
+    fused_hidden<kInPad>(w1, st_b1, bufx, buf1, wv, lane);
+    __syncthreads();   // and wavefront 0 has left the last tile's correction
+    if constexpr (FROM_Q) store_operands();
+    fused_hidden<kHidden>(w2, st_b2, buf1, buf2, wv, lane);
+    store_inputs();    // every wavefront has left the first layer
     __syncthreads();
     f32x4 acc = bv3;
+    bf16x8 b[kHidden / 32], w3[kHidden / 32];
 #pragma unroll
     for (int ks = 0; ks < kHidden / 32; ++ks) {
-      const bf16x8 b = *reinterpret_cast<const bf16x8 *>(buf0 + (16 * mt + r) * kLd + 32 * ks + kq);
-      const bf16x8 w3 = *reinterpret_cast<const bf16x8 *>(st_w3 + (16 * nt + r) * kLd + 32 * ks + kq);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3, b, acc, 0, 0, 0);
+      b[ks] = *reinterpret_cast<const bf16x8 *>(buf2 + (16 * mt + r) * kHidden + swz(4 * ks + kc, r));
+      w3[ks] = *reinterpret_cast<const bf16x8 *>(st_w3 + (16 * nt + r) * kHidden + swz(4 * ks + kc, r));
     }
+#pragma unroll
+    for (int ks = 0; ks < kHidden / 32; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3[ks], b[ks], acc, 0, 0, 0);
     const f32x4 out = acc;
     if constexpr (!FROM_Q) {
       const int e = e0 + 16 * mt + r;
       if (e < rows) *reinterpret_cast<f32x4 *>(Y + (size_t)e * kOutPad + n0) = out;
     } else {
-      // outputs to LDS (the first hidden layer's buffer is free), then one
-      // lane per row forms its element's correction (wavefront 0)
+      // outputs to LDS, then one lane per row forms its element's correction
+      // (wavefront 0, while the others go on to the next tile's first layer)
       // (unit n of row i at n kYs + i: conflict-free stores and lane-per-row reads)
-      float *ys = reinterpret_cast<float *>(buf1);
 #pragma unroll
       for (int i = 0; i < 4; ++i) ys[(n0 + i) * kYs + 16 * mt + r] = out[i];
       __syncthreads();
@@ -358,7 +422,6 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp_fused(const T *__restrict__
         mass += m;
       }
     }
-    __syncthreads();   // the next tile overwrites both buffers
   }
   if constexpr (FROM_Q) {
     if (wv == 0 && lane == 0) {
