@@ -85,8 +85,6 @@ struct TrainUpdate {
 };
 hipError_t launch_train(const TrainRows &r, const TrainDw &d, const TrainUpdate &u, hipStream_t s);
 hipError_t launch_unpad(const float *G, int k_in, int n_out, int np_, float *out, hipStream_t s);
-hipError_t launch_features(int dtype, const void *q, int n_lon, int n_lat, const float *mean, const float *istd,
-                           int ldx, __bf16 *X, hipStream_t s);
 hipError_t launch_features_f32(int dtype, const void *q, int n_lon, int n_lat, const float *mean, const float *istd,
                                float *X, hipStream_t s);
 hipError_t launch_project(int dtype, const void *q, int n_lon, int E, int np, int nk, const double *P,
