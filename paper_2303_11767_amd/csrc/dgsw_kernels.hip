@@ -59,8 +59,21 @@ __global__ __attribute__((amdgpu_waves_per_eu(MORE ? 3 : 4))) __launch_bounds__(
       threadIdx.x, (lds_double *)sh);
 }
 
+// Wavefronts a SIMD that the registers have to allow, where the compiler by
+// itself takes a few registers more than the LDS would let run: r = 6 FP32 171
+// registers and two instead of three (360x180 49.1 -> 45.4 us a stage, 720x360
+// 166 -> 156), r = 4 FP64 dq/dt 257 and one instead of two (56 -> 43 us at
+// 360x180).  Elsewhere the limit costs more in spills than it brings (r = 5 FP32
+// 36 us with three, 43 with four; r = 4 FP64 with a combination 45 and 49).
+template <typename T, int NP, int CM, bool STRIPS>
+constexpr int stage_waves() {
+  if (!STRIPS) return 1;
+  return sizeof(T) == 8 ? (NP == 5 && CM == 0 ? 2 : 1) : (NP == 7 ? 3 : 1);
+}
+
 template <typename T, int NP, int WPB, int CM, bool STRIPS>
-__global__ __launch_bounds__(64 * WPB) void k_dg_stage(StageArgs<T, NP> A, int segs) {
+__global__ __attribute__((amdgpu_waves_per_eu(stage_waves<T, NP, CM, STRIPS>())))
+__launch_bounds__(64 * WPB) void k_dg_stage(StageArgs<T, NP> A, int segs) {
   using S_ = Shape<T, NP>;
   // WPB independent wavefronts per workgroup (fewer workgroups to dispatch on
   // large meshes); each wavefront has its own LDS slice and never waits for

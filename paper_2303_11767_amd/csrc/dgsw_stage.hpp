@@ -97,11 +97,14 @@ struct Shape {
   // busy 83 % of the stage).  With STRIPS the wavefront's data comes and goes in
   // contiguous runs of whole elements instead: straight into LDS, before the
   // arrays above take their place, the element west of the segment, the segment,
-  // the element east of it, and the segment's northern and southern neighbours;
-  // the stage's other states and the result value by value.
+  // the element east of it and the segment's northern neighbours; its southern
+  // ones, the stage's other states and the result value by value (the southern
+  // ones wait in registers until the others have been read: beside them they
+  // would cost wavefronts, FP64 r = 4 seven instead of eight a CU).
   static constexpr bool UNALIGNED = ROWALIGN < 16;
   static constexpr int EL = 3 * N;                      // values of an element
-  static constexpr int oOwn = EL, oN = (GPW + 2) * EL, oS = oN + GPW * EL, STRIP = oS + GPW * EL;
+  static constexpr int oOwn = EL, oN = (GPW + 2) * EL, STRIP = oN + GPW * EL;
+  static constexpr int SREG = (GPW * EL + 63) / 64;     // southern values of a lane
   static constexpr int wave(bool strips) {              // LDS values of a wavefront
     return strips ? cmax((GPW + 1) * SH, STRIP) : (GPW + 1) * SH;
   }
@@ -386,6 +389,7 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   const size_t row_off = (size_t)t * NP;
   const size_t base = (size_t)e * 3 * N + row_off;
   T qr[3][NP], xE[3][NP], xW[3][NP], xN[3][NP], xS[3][NP];
+  T sv[STRIPS ? S_::SREG : 1];
   if constexpr (STRIPS) {
     constexpr int WPV = sizeof(T) / 4;                       // 4-byte words per value
     const T *qrow = q + (size_t)(j * n_lon) * EL, *own = qrow + (size_t)i0 * EL;
@@ -399,11 +403,14 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
     if (cnt == GPW) {
       strip_to_lds<GPW * EL * WPV, true>(own, 0, w + S_::oOwn * WPV, lane);
       strip_to_lds<GPW * EL * WPV, true>(nrow, 0, w + S_::oN * WPV, lane);
-      strip_to_lds<GPW * EL * WPV, true>(srow, 0, w + S_::oS * WPV, lane);
+#pragma unroll
+      for (int k = 0; k < S_::SREG; ++k)
+        sv[k] = srow[64 * (k + 1) <= GPW * EL || 64 * k + lane < GPW * EL ? 64 * k + lane : 0];
     } else {
       strip_to_lds<GPW * EL * WPV, false>(own, cnt * EL * WPV, w + S_::oOwn * WPV, lane);
       strip_to_lds<GPW * EL * WPV, false>(nrow, cnt * EL * WPV, w + S_::oN * WPV, lane);
-      strip_to_lds<GPW * EL * WPV, false>(srow, cnt * EL * WPV, w + S_::oS * WPV, lane);
+#pragma unroll
+      for (int k = 0; k < S_::SREG; ++k) sv[k] = srow[64 * k + lane < cnt * EL ? 64 * k + lane : 0];
     }
   } else {
     const int eE = (i + 1 == n_lon) ? e + 1 - n_lon : e + 1;
@@ -453,7 +460,7 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
     // row b = t of the element and of its longitude neighbours, column a = t of
     // the latitude ones (lanes without an element read the segment's last)
     const int ge = i - i0;
-    const T *o = sh + S_::oOwn + ge * EL, *oN = sh + S_::oN + ge * EL, *oS = sh + S_::oS + ge * EL;
+    const T *o = sh + S_::oOwn + ge * EL, *oN = sh + S_::oN + ge * EL, *oS = sh + ge * EL;
 #pragma unroll
     for (int v = 0; v < 3; ++v)
 #pragma unroll
@@ -462,8 +469,16 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
         xE[v][k] = o[EL + v * N + t * NP + k];
         xW[v][k] = o[-EL + v * N + t * NP + k];
         xN[v][k] = oN[v * N + k * NP + t];
-        xS[v][k] = oS[v * N + k * NP + t];
       }
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < S_::SREG; ++k)
+      if (64 * (k + 1) <= GPW * EL || 64 * k + lane < GPW * EL) sh[64 * k + lane] = sv[k];
+    wave_sync();
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+#pragma unroll
+      for (int k = 0; k < NP; ++k) xS[v][k] = oS[v * N + k * NP + t];
     wave_sync();
   }
 
