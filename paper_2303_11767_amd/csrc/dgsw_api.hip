@@ -47,7 +47,7 @@ void release(dg_ctx *c) {
   if (c->d_rows) (void)hipFree(c->d_rows);
   if (c->d_mass_w) (void)hipFree(c->d_mass_w);
   if (c->d_partial) (void)hipFree(c->d_partial);
-  if (c->d_out4) (void)hipFree(c->d_out4);
+  if (c->h_out4) (void)hipHostFree(c->h_out4);
   if (c->d_proj) (void)hipFree(c->d_proj);
   delete c;
 }
@@ -181,10 +181,10 @@ int make_ctx(const dg_mesh_desc *desc, const dgsw::HostTables &t, hipStream_t s,
       (e = hipMalloc(&c->d_rows, rb)) != hipSuccess ||
       (e = hipMalloc(reinterpret_cast<void **>(&c->d_mass_w), t.mass_w.size() * sizeof(double))) != hipSuccess ||
       (e = hipMalloc(reinterpret_cast<void **>(&c->d_partial), dgsw::mass_blocks() * 4 * sizeof(double))) != hipSuccess ||
-      (e = hipMalloc(reinterpret_cast<void **>(&c->d_out4), 4 * sizeof(double))) != hipSuccess ||
+      (e = hipHostMalloc(reinterpret_cast<void **>(&c->h_out4), 4 * sizeof(double), hipHostMallocDefault)) != hipSuccess ||
       (e = hipMalloc(reinterpret_cast<void **>(&c->d_proj), proj.size() * sizeof(double))) != hipSuccess) {
     release(c);
-    return fail(DG_ENOMEM, std::string("hipMalloc of context tables: ") + hipGetErrorString(e));
+    return fail(DG_ENOMEM, std::string("allocation of context tables: ") + hipGetErrorString(e));
   }
   if ((e = hipMemcpyAsync(c->d_glob, hg.data(), gb, hipMemcpyHostToDevice, s)) != hipSuccess ||
       (e = hipMemcpyAsync(c->d_rows, hr.data(), rb, hipMemcpyHostToDevice, s)) != hipSuccess ||
@@ -552,12 +552,10 @@ int dg_mass(dg_ctx *ctx, const void *q, double out[3], void *hip_stream) {
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e = dgsw::launch_mass(ctx->d.dtype == DG_F64 ? 0 : 1, ctx->np, q, ctx->d_mass_w,
                                    ctx->d.n_lon, ctx->E, ctx->levels, ctx->d_partial,
-                                   ctx->d_out4, s);
+                                   ctx->h_out4, s);
   if (e != hipSuccess) return hip_fail(e, "mass kernel launch");
-  double h4[4];
-  if ((e = hipMemcpyAsync(h4, ctx->d_out4, sizeof(h4), hipMemcpyDeviceToHost, s)) != hipSuccess)
-    return hip_fail(e, "mass copy-out");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "mass synchronise");
+  const double h4[4] = {ctx->h_out4[0], ctx->h_out4[1], ctx->h_out4[2], ctx->h_out4[3]};
   out[0] = h4[0];
   out[1] = h4[1];
   out[2] = h4[2];

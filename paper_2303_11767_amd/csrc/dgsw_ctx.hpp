@@ -18,7 +18,9 @@ struct dg_ctx {
   size_t glob_bytes = 0, rows_bytes = 0;   // sizes of the two
   double *d_mass_w = nullptr;  // mass diagnostic weights [n_lat][np]
   double *d_partial = nullptr; // mass partial sums
-  double *d_out4 = nullptr;    // mass result
+  // mass result: pinned host memory the last kernel writes itself (a copy to
+  // pageable memory after it cost 8 us more a call)
+  double *h_out4 = nullptr;
   const void *forcing = nullptr;
   double min_width = 0.0;
   double *d_proj = nullptr;    // cos-weighted projection onto order k = 0..7: blocks
