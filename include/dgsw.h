@@ -276,8 +276,8 @@ int dg_ens_set_schedule(dg_ens *ens, int32_t waves_per_group, int32_t groups, in
 int dg_ens_get_schedule(const dg_ens *ens, int32_t *waves_per_group, int32_t *groups,
                         int32_t *fused);
 /* Stage-kernel layout (DG_KERNEL_*, as dg_set_kernel) of every member of the
- * given order; at dg_ens_init each member takes the layout a single mesh of
- * its size and order would take.  DG_EINVAL if no member has that order, if
+ * given order; at dg_ens_init the members of an order take the layout that a
+ * single mesh of their total size would take.  DG_EINVAL if no member has that order, if
  * the schedule is the fused launch and kernel is not DG_KERNEL_LINE, or while
  * graphs of the ensemble are live.  The schedule's settings are kept. */
 int dg_ens_set_kernel(dg_ens *ens, int32_t order, int32_t kernel);

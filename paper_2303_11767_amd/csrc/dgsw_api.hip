@@ -86,6 +86,24 @@ const char *dg_last_error(void) { return dgsw::last_error(); }
 
 }  // extern "C"
 
+// Kernel layout of a mesh, or of the members of one order of an ensemble, from the
+// number of wavefronts of its line layout; chosen from MI355X stage timings of both layouts over
+// r = 1..5, 90x45 .. 1440x720 and both precisions: the half layout for FP64 at
+// r = 1 (1440x720 91 us a stage against 97), r = 3 (the matrix-core stage) and
+// r >= 5 (the line layout's registers allow one wavefront per SIMD), and
+// wherever the line layout has few wavefronts.  Up to how many, by order (half
+// / line, us a stage): r = 1 FP32 3072 (360x180, 2160 wavefronts: 5.7 / 6.0;
+// 512x256, 4096: 8.6 / 7.7); r = 2 1024 (FP32 180x90, 810: 5.7 / 5.7; 270x135,
+// 1755: 8.5 / 7.1; FP64 7.4 / 7.9 and 11.3 / 10.6); r = 3 FP32 2048 (180x90, 1080:
+// 5.8 / 6.9; 270x135, 2295: 8.9 / 9.2; 360x180, 4140: - / 13.5); r = 4 512, where
+// the work the two halves duplicate costs more (FP32 120x60, 600: 7.8 / 7.5;
+// FP64 90x45, 360: 7.4 / 9.9); r = 5 FP32 1600 (135x68, 952: 8.6 / 9.6; 180x90,
+// 1620: 12.2 / 12.3).  dg_autotune measures instead.
+int dgsw::default_layout(bool f64, int r, long long waves_line) {
+  const int few = r == 1 ? 3072 : (r == 2 ? 1024 : (r <= 3 ? 2048 : (r == 5 ? 1600 : 512)));
+  return (f64 && (r == 1 || r == 3 || r >= 5)) || waves_line <= few ? DG_KERNEL_HALF : DG_KERNEL_LINE;
+}
+
 namespace {
 
 // Context from validated parameters and the host tables of its geometry.
@@ -93,26 +111,8 @@ int make_ctx(const dg_mesh_desc *desc, const dgsw::HostTables &t, hipStream_t s,
   dg_ctx *c = new dg_ctx();
   c->d = *desc;
   c->periodic_y = t.periodic_y ? 1 : 0;
-  // kernel layout, chosen from MI355X stage timings of both layouts over
-  // r = 1..5, 90x45 .. 1440x720 and both precisions: the half layout for FP64 at
-  // r = 1 (1440x720 91 us a stage against 97), r = 3 (the matrix-core stage) and
-  // r >= 5 (the line layout's registers allow one wavefront per SIMD), and
-  // wherever the line layout has few wavefronts.  Up to how many, by order (half
-  // / line, us a stage): r = 1 FP32 3072 (360x180, 2160 wavefronts: 5.7 / 6.0;
-  // 512x256, 4096: 8.6 / 7.7); r = 2 1024 (FP32 180x90, 810: 5.7 / 5.7; 270x135,
-  // 1755: 8.5 / 7.1; FP64 7.4 / 7.9 and 11.3 / 10.6); r = 3 FP32 2048 (180x90, 1080:
-  // 5.8 / 6.9; 270x135, 2295: 8.9 / 9.2; 360x180, 4140: - / 13.5); r = 4 512, where
-  // the work the two halves duplicate costs more (FP32 120x60, 600: 7.8 / 7.5;
-  // FP64 90x45, 360: 7.4 / 9.9); r = 5 FP32 1600 (135x68, 952: 8.6 / 9.6; 180x90,
-  // 1620: 12.2 / 12.3).  dg_autotune measures instead.
-  {
-    const int waves_line = dgsw::waves_per_row(desc->order + 1, desc->n_lon) * desc->n_lat;
-    const bool f64 = desc->dtype == DG_F64;
-    const int r = desc->order;
-    const int few = r == 1 ? 3072 : (r == 2 ? 1024 : (r <= 3 ? 2048 : (r == 5 ? 1600 : 512)));
-    const bool half = (f64 && (r == 1 || r == 3 || r >= 5)) || waves_line <= few;
-    c->kernel = half ? DG_KERNEL_HALF : DG_KERNEL_LINE;
-  }
+  c->kernel = dgsw::default_layout(desc->dtype == DG_F64, desc->order,
+                                   (long long)dgsw::waves_per_row(desc->order + 1, desc->n_lon) * desc->n_lat);
   c->np = desc->order + 1;
   c->N = c->np * c->np;
   c->E = desc->n_lon * desc->n_lat;

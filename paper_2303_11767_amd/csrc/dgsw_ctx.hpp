@@ -39,4 +39,5 @@ namespace dgsw {
 int fail(int code, const std::string &msg);
 int hip_fail(hipError_t e, const char *what);
 bool aligned16(const void *p);
+int default_layout(bool f64, int order, long long waves_line);   // DG_KERNEL_LINE or DG_KERNEL_HALF
 }  // namespace dgsw
