@@ -80,7 +80,8 @@ __device__ __forceinline__ float gelu_and_grad(float &z) {
 // first load takes about 10 k).  Inputs have a buffer of their own, so a tile
 // has three barriers and the next tile's operands are fetched meanwhile: with
 // the operands fetched at the tile's start and rows padded instead of permuted
-// 40.0 us for 64 800 rows, now 36.8; weights streamed from L2 for two
+// 40.0 us for 64 800 rows, now 35.9 (36.8 before the weights were requested
+// behind the first tile's inputs); weights streamed from L2 for two
 // workgroups per CU took 38.8.
 constexpr int kRows = 64;                 // rows per tile
 constexpr int kMlpGrid = 256;             // persistent workgroups: one per MI355X compute unit
@@ -222,38 +223,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(64 * kWa
   __shared__ float st_fm[FROM_Q ? kFeatures : 1], st_fi[FROM_Q ? kFeatures : 1];
   int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // the output layer's weights in LDS (chunks permuted like the activations):
-  // registers held for 8 products per tile would push the kernel into scratch
-  for (int c = tid; c < kOutPad * kHidden / 8; c += 64 * kWaves) {
-    const int u = c / (kHidden / 8), k8 = c - u * (kHidden / 8);
-    *reinterpret_cast<bf16x8 *>(st_w3 + u * kHidden + swz(k8, u)) =
-        *reinterpret_cast<const bf16x8 *>(W3t + (size_t)u * kHidden + 8 * k8);
-  }
-  // the hidden layers' weights in registers, requested after the LDS tables
-  // (loads complete in order: the tables' stores wait only for their own
-  // loads, and these arrive while the first tile's inputs are fetched)
-  bf16x8 w1[kInPad / 32][2], w2[kHidden / 32][2];
   // output layer: wavefront wv takes rows [16 (wv / 2), +16) and units [16 (wv % 2), +16)
   const int mt = wv >> 1, nt = wv & 1;
-  const f32x4 bv3 = *reinterpret_cast<const f32x4 *>(b3p + 16 * nt + (lane >> 4) * 4);
-  // zero padding of the inputs beyond the 108 features (never overwritten)
-  for (int idx = tid; idx < kRows * (kInPad - kFeatures) / 4; idx += 64 * kWaves) {
-    const int rr = idx / ((kInPad - kFeatures) / 4), k = kFeatures + 4 * (idx - rr * ((kInPad - kFeatures) / 4));
-    *reinterpret_cast<bf16x4 *>(bufx + rr * kInPad + swz(k >> 3, rr) + (k & 4)) = bf16x4{};
-  }
-  if (tid < kHidden)
-    st_b1[tid] = b1[tid];
-  else
-    st_b2[tid - kHidden] = b2[tid - kHidden];
-  if constexpr (FROM_Q) {
-    for (int k = tid; k < kFeatures; k += 64 * kWaves) {
-      st_fm[k] = fmean[k];
-      st_fi[k] = fistd[k];
-    }
-  }
-  load_hidden<kInPad>(W1f, wv, lane, w1);
-  load_hidden<kHidden>(W2f, wv, lane, w2);
-  __syncthreads();            // the tables above before their first use
   double mass = 0.0;          // wavefront 0: this workgroup's h-mass of the corrections
   bool any_fell = false;
   unsigned long long fell_count = 0ull;
@@ -364,6 +335,46 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(64 * kWa
   };
   const int ntiles = (rows + kRows - 1) / kRows;
   load_tile(blockIdx.x * kRows, blockIdx.x * kRows);
+  // the tables in LDS, all loads issued before any is waited for: the output
+  // layer's weights (chunks permuted like the activations; registers held for
+  // 8 products per tile would push the kernel into scratch), the biases, the
+  // feature standardisation
+  constexpr int kChunks = kOutPad * kHidden / 8 / (64 * kWaves);
+  static_assert(kOutPad * kHidden == 8 * 64 * kWaves * kChunks && 2 * kHidden == 64 * kWaves && kFeatures <= 64 * kWaves,
+                "table copies");
+  bf16x8 w3c[kChunks];
+#pragma unroll
+  for (int n = 0; n < kChunks; ++n) w3c[n] = *reinterpret_cast<const bf16x8 *>(W3t + 8 * (tid + 64 * kWaves * n));
+  const float bias = tid < kHidden ? b1[tid] : b2[tid - kHidden];
+  const int kf = tid < kFeatures ? tid : 0;
+  const float fm = FROM_Q ? fmean[kf] : 0.f, fi = FROM_Q ? fistd[kf] : 0.f;
+  const f32x4 bv3 = *reinterpret_cast<const f32x4 *>(b3p + 16 * nt + (lane >> 4) * 4);
+  // the hidden layers' weights in registers, requested after the first tile's
+  // operands and the LDS tables (loads complete in order: the tables and the
+  // inputs wait only for their own, and the second layer's weights arrive
+  // during the first layer)
+  bf16x8 w1[kInPad / 32][2], w2[kHidden / 32][2];
+  load_hidden<kInPad>(W1f, wv, lane, w1);
+  load_hidden<kHidden>(W2f, wv, lane, w2);
+#pragma unroll
+  for (int n = 0; n < kChunks; ++n) {
+    const int c = tid + 64 * kWaves * n, u = c / (kHidden / 8), k8 = c - u * (kHidden / 8);
+    *reinterpret_cast<bf16x8 *>(st_w3 + u * kHidden + swz(k8, u)) = w3c[n];
+  }
+  if (tid < kHidden)
+    st_b1[tid] = bias;
+  else
+    st_b2[tid - kHidden] = bias;
+  if (FROM_Q && tid < kFeatures) {
+    st_fm[tid] = fm;
+    st_fi[tid] = fi;
+  }
+  // zero padding of the inputs beyond the 108 features (never overwritten)
+  for (int idx = tid; idx < kRows * (kInPad - kFeatures) / 4; idx += 64 * kWaves) {
+    const int rr = idx / ((kInPad - kFeatures) / 4), k = kFeatures + 4 * (idx - rr * ((kInPad - kFeatures) / 4));
+    *reinterpret_cast<bf16x4 *>(bufx + rr * kInPad + swz(k >> 3, rr) + (k & 4)) = bf16x4{};
+  }
+  __syncthreads();            // the tables above before their first use
   store_inputs();
   __syncthreads();
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
