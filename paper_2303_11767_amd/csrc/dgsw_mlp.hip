@@ -536,8 +536,9 @@ hipError_t launch_prep_weights(const float *P, const PrepWeights &w, hipStream_t
 //   k_train_update  the ranges' sums in order, and Adam.
 // The 29 launches this replaces (one GEMM, conversion, column sum or copy
 // each) took 157 us at 8192 rows, launches and memory round trips almost all of
-// it; these take 37 (rows 21.8, one tile per CU: a serial chain of five products
-// and their barriers; gradients 8.7, update 5.2, weights 3).  Rounding points as before: BF16 factors of every product, FP32
+// it; these take 34.9 (rows 20.5, one tile per CU: a serial chain of five
+// products and their barriers, 27 k cycles; gradients 8.8, update 5.2, weights
+// 3).  Rounding points as before: BF16 factors of every product, FP32
 // accumulation, bias, GELU, loss and gradients in FP32.
 constexpr int kTrRows = 32;               // rows of a tile: one K block of the weight gradients
 constexpr int kLdX = kInPad + 8, kLdY = kOutPad + 8;   // LDS row strides in BF16
@@ -596,6 +597,17 @@ __device__ __forceinline__ void train_gelu(f32x4 (&z)[2][2], const float *__rest
   }
 }
 
+// Sum over the 16 lanes of a row group, in every lane of it, by rotations within
+// the group (the vector unit's own lane moves: the LDS permutes of __shfl_xor
+// are a round trip each; the pairs added are the same).
+template <int ROT>
+__device__ __forceinline__ float add_rotated(float t) {
+  return t + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x120 + ROT, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float sum16(float t) {
+  return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(t))));
+}
+
 // d = acc gelu' as BF16 into LDS; its sum over the tile's rows added to db
 // (lanes of one 16-lane group hold the rows of a unit; lane % 16 == 0 the sum).
 __device__ __forceinline__ void train_gelu_grad(const f32x4 (&acc)[2][2], const f32x4 (&gp)[2][2], __bf16 *out, int wv,
@@ -617,10 +629,7 @@ __device__ __forceinline__ void train_gelu_grad(const f32x4 (&acc)[2][2], const 
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float t = d[0][i] + d[1][i];
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-      db[nt][i] += t;
+      db[nt][i] += sum16(d[0][i] + d[1][i]);
     }
   }
 }
@@ -630,7 +639,7 @@ __device__ __forceinline__ void train_gelu_grad(const f32x4 (&acc)[2][2], const 
 __device__ __forceinline__ void train_fragments(const __bf16 *in, int ld, int units, __bf16 *__restrict__ out, int wv,
                                                 int lane) {
   const int r = lane & 15, kq = (lane >> 4) * 8;
-#pragma unroll 1
+#pragma unroll 2
   for (int u = wv; u < units / 16; u += kWaves) {
     bf16x8 f;
 #pragma unroll
@@ -661,7 +670,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * kWaves
     const int lane = tid & 63, r = lane & 15;
     const size_t row0 = (size_t)tile * kTrRows;
     bf16x8 w1[kInPad / 32][2], w2[kHidden / 32][2];
-    // inputs (any alignment of X), then the forward weights: loads complete in order
+    // inputs (any alignment of X), then the first layer's weights: loads complete
+    // in order, and more of them in front of the LDS stores would hold those back
     float xv[(kTrRows * kFeatures + 64 * kWaves - 1) / (64 * kWaves)];
 #pragma unroll
     for (int n = 0; n < (int)(sizeof(xv) / sizeof(float)); ++n) {
@@ -669,7 +679,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * kWaves
       xv[n] = idx < kTrRows * kFeatures ? a.X[row0 * kFeatures + idx] : 0.f;
     }
     train_weights<kInPad>(a.w.W1f, wv, lane, w1);
-    train_weights<kHidden>(a.w.W2f, wv, lane, w2);
 #pragma unroll
     for (int n = 0; n < (int)(sizeof(xv) / sizeof(float)); ++n) {
       const int idx = tid + 64 * kWaves * n;
@@ -680,6 +689,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * kWaves
     __syncthreads();
     f32x4 z1[2][2], z2[2][2], acc[2][2];
     train_product<kInPad>(w1, sx, kLdX, lane, z1);
+    train_weights<kHidden>(a.w.W2f, wv, lane, w2);
     train_gelu(z1, a.P + ob1, sh1, wv, lane);
     __syncthreads();
     train_product<kHidden>(w2, sh1, kLd, lane, z2);
@@ -700,7 +710,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * kWaves
     train_weights<kOutPad>(a.w.W3rf, wv, lane, w3r);
     train_gelu(z2, a.P + ob2, sh2, wv, lane);
     __syncthreads();
-    train_weights<kHidden>(a.w.W2rf, wv, lane, w2);
     if (wv < 4) {
       f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -718,13 +727,11 @@ __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * kWaves
           g = 2.f * d * a.scale;
         }
         h[i] = (__bf16)g;
-        float t = g;
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-        db3[i] += t;
+        db3[i] += sum16(g);
       }
       *reinterpret_cast<bf16x4 *>(sdy + (16 * mt + r) * kLdY + n0) = h;
     }
+    train_weights<kHidden>(a.w.W2rf, wv, lane, w2);
     __syncthreads();
     train_product<kOutPad>(w3r, sdy, kLdY, lane, acc);
     train_gelu_grad(acc, z2, sd2, wv, lane, db2);
