@@ -7,9 +7,11 @@ namespace dgsw {
 
 // PK: wavefront w of a layer takes the GPW consecutive elements from w GPW on,
 // across row ends (needs GPW <= n_lon; ceil(E / GPW) wavefronts); otherwise
-// row-aligned segments, segs per row.  One wavefront per workgroup.  Register budget: two wavefronts per SIMD (256 registers), which
-// keeps the FP64 r >= 5 cases, at the edge of 256, from spilling into
-// accumulation registers and halving their occupancy.
+// row-aligned segments, segs per row.  One wavefront per workgroup (two or four
+// were no faster: r = 1 FP64 360x180 8.4 us with one, 8.3 with four, 64x32 3.4 and
+// 4.0).  Register budget: two wavefronts per SIMD (256 registers), which keeps the
+// FP64 r >= 5 cases, at the edge of 256, from spilling into accumulation
+// registers and halving their occupancy.
 template <typename T, int NP, int WPB, int CM, bool PK>
 __global__ __attribute__((amdgpu_waves_per_eu(2))) __launch_bounds__(64 * WPB) void k_dg_stage_h2(
     StageArgs<T, NP> A, int segs) {
@@ -237,9 +239,9 @@ static hipError_t launch_stage_t(const StageLaunch &a, hipStream_t s) {
   const int waves = segs * a.n_lat * a.levels;
   // Strips (rows that are not 16-byte aligned): in FP32 always, in FP64, where
   // their LDS costs wavefronts, on meshes that fill the GPU several times.  Stage
-  // times, rows / strips, 720x360: r = 2 FP32 29.6 / 26.6 us, r = 4 94.9 / 74.5,
-  // r = 5 132 / 108, FP64 r = 2 62.4 / 51.9, r = 4 179 / 158; FP64 r = 2 360x180 (3240
-  // wavefronts) 18.2 / 18.9, r = 4 360x180 (5400) 48.1 / 45.7, 180x90 (1350) 15.5 /
+  // times, rows / strips, 720x360: r = 2 FP32 29.6 / 26.6 us, r = 4 94.9 / 69.0,
+  // r = 5 132 / 110, FP64 r = 2 62.4 / 52.0, r = 4 179 / 146; FP64 r = 2 360x180 (3240
+  // wavefronts) 18.2 / 18.9, r = 4 360x180 (5400) 48.1 / 43.5, 180x90 (1350) 15.5 /
   // 15.8; rows that are aligned are faster as rows (r = 3 FP32 38.2 / 41.3).  One
   // wavefront per workgroup then (their LDS, r = 5 FP32 720x360 134 us with four);
   // with rows four on large meshes.

@@ -536,8 +536,8 @@ hipError_t launch_prep_weights(const float *P, const PrepWeights &w, hipStream_t
 //   k_train_update  the ranges' sums in order, and Adam.
 // The 29 launches this replaces (one GEMM, conversion, column sum or copy
 // each) took 157 us at 8192 rows, launches and memory round trips almost all of
-// it; these take 34.9 (rows 20.5, one tile per CU: a serial chain of five
-// products and their barriers, 27 k cycles; gradients 8.8, update 5.2, weights
+// it; these take 33.1 (rows 19.5, one tile per CU: a serial chain of five
+// products and their barriers, 27 k cycles; gradients 8.9, update 5.4, weights
 // 3).  Rounding points as before: BF16 factors of every product, FP32
 // accumulation, bias, GELU, loss and gradients in FP32.
 constexpr int kTrRows = 32;               // rows of a tile: one K block of the weight gradients
@@ -776,66 +776,48 @@ int train_row_blocks(int rows) {
   return t < kMaxTrainBlocks ? t : kMaxTrainBlocks;
 }
 
-// Weight gradients: a workgroup takes 64 x 64 outputs (64 x 32 of the output
-// layer's) of one matrix over one range of rows; its eight wavefronts take
-// every eighth block of 32 rows (eight fragments of a kilobyte, sixteen MFMAs
-// each) and their sums meet in LDS.  28 workgroups a range: 16 of W2, 8 of W1,
-// 4 of W3.  The fragments come from other XCDs' caches, so latency bounds it:
-// a wavefront has two blocks at 8192 rows, all its loads in flight at once, and
-// a range belongs to one XCD (8.7 us at 8192 rows; 11.0 with the ranges spread
-// over all XCDs, 10.2 with one wavefront per output tile and 256 rows).
-constexpr int kDwWaves = 8, kDwJobs = 28;
+// Weight gradients: a wavefront takes 32 x 64 outputs (32 x 32 of the output
+// layer's) of one matrix over one range of rows, block of 32 rows by block (six
+// fragments of a kilobyte, eight MFMAs each).  The four wavefronts of a
+// workgroup share the activations (of the output layer's: the gradients); 14
+// workgroups a range: 8 of W2, 4 of W1, 2 of W3.  The fragments come from other
+// XCDs' caches, so latency bounds it: four blocks' loads are in flight at once,
+// and a range belongs to one XCD.  Ranges of 256 rows, each summed in order and
+// then the ranges in order, fix the bits of the gradients.  8192 rows: 8.9 us
+// (10.2 with 64 x 64 outputs a wavefront; with ranges of 512 rows split over the
+// wavefronts of a workgroup 8.7).
+constexpr int kDwWaves = 4, kDwJobs = 14;
 
 template <int NT>
 __device__ __forceinline__ void train_dw(const __bf16 *__restrict__ A, int ua, const __bf16 *__restrict__ B, int ub,
-                                         int c0, int c1, int wv, int lane, f32x4 *sh, float *__restrict__ C, int ldc) {
-  f32x4 acc[4][NT];
+                                         int c0, int c1, int lane, float *__restrict__ C, int ldc) {
+  constexpr int MT = 2;
+  f32x4 acc[MT][NT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-  for (int c = c0 + wv; c < c1; c += kDwWaves) {
-    bf16x8 a[4], b[NT];
+#pragma unroll 4
+  for (int c = c0; c < c1; ++c) {
+    bf16x8 a[MT], b[NT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(A + ((size_t)c * ua + i) * 512 + lane * 8);
+    for (int i = 0; i < MT; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(A + ((size_t)c * ua + i) * 512 + lane * 8);
 #pragma unroll
     for (int j = 0; j < NT; ++j) b[j] = *reinterpret_cast<const bf16x8 *>(B + ((size_t)c * ub + j) * 512 + lane * 8);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
   }
-  // wavefronts 4 .. 7 to LDS, added by 0 .. 3; those four again, and
-  // wavefront w adds the tiles (i, j) of row i = w
-  f32x4 *mine = sh + (wv & 3) * (4 * NT * 64) + lane;
-  if (wv >= 4) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int j = 0; j < NT; ++j) mine[(i * NT + j) * 64] = acc[i][j];
-  }
-  __syncthreads();
-  if (wv < 4) {
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) mine[(i * NT + j) * 64] += acc[i][j];
-  }
-  __syncthreads();
-  if (wv < 4) {
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const f32x4 *t = sh + (wv * NT + j) * 64 + lane;
-      const f32x4 v = (t[0] + t[4 * NT * 64]) + (t[8 * NT * 64] + t[12 * NT * 64]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) C[(size_t)(16 * wv + (lane >> 4) * 4 + e) * ldc + 16 * j + (lane & 15)] = v[e];
-    }
-  }
+      for (int e = 0; e < 4; ++e) C[(size_t)(16 * i + (lane >> 4) * 4 + e) * ldc + 16 * j + (lane & 15)] = acc[i][j][e];
 }
 
 __global__ __launch_bounds__(64 * kDwWaves) void k_train_dw(TrainDw a) {
-  __shared__ f32x4 sh[4 * 16 * 64];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // workgroups are dispatched round-robin over the 8 XCDs: each takes a
@@ -846,22 +828,22 @@ __global__ __launch_bounds__(64 * kDwWaves) void k_train_dw(TrainDw a) {
   const int c0 = range * a.per, c1 = c0 + a.per < a.chunks ? c0 + a.per : a.chunks;
   float *G = a.part + (size_t)range * kGradPart;
   constexpr int UH = kHidden / 16, UX = kInPad / 16, UY = kOutPad / 16;
-  if (job < 16) {
-    const int m = job >> 2, n = job & 3;
-    train_dw<4>(a.H1f + m * 4 * 512, UH, a.D2f + n * 4 * 512, UH, c0, c1, wv, lane, sh,
-                G + oG2 + (size_t)m * 64 * kHidden + n * 64, kHidden);
-  } else if (job < 24) {
-    const int m = (job - 16) >> 2, n = job & 3;
-    train_dw<4>(a.Xf + m * 4 * 512, UX, a.D1f + n * 4 * 512, UH, c0, c1, wv, lane, sh,
-                G + oG1 + (size_t)m * 64 * kHidden + n * 64, kHidden);
+  static_assert(kHidden == 64 * kDwWaves && kHidden == 8 * 32 && kInPad == 4 * 32 && kOutPad == 32, "jobs");
+  if (job < 8) {
+    train_dw<4>(a.H1f + job * 2 * 512, UH, a.D2f + wv * 4 * 512, UH, c0, c1, lane,
+                G + oG2 + (size_t)job * 32 * kHidden + wv * 64, kHidden);
+  } else if (job < 12) {
+    const int m = job - 8;
+    train_dw<4>(a.Xf + m * 2 * 512, UX, a.D1f + wv * 4 * 512, UH, c0, c1, lane,
+                G + oG1 + (size_t)m * 32 * kHidden + wv * 64, kHidden);
   } else {
-    const int m = job - 24;
-    train_dw<2>(a.H2f + m * 4 * 512, UH, a.DYf, UY, c0, c1, wv, lane, sh, G + oG3 + (size_t)m * 64 * kOutPad, kOutPad);
+    const int m = (job - 12) * kDwWaves + wv;
+    train_dw<2>(a.H2f + m * 2 * 512, UH, a.DYf, UY, c0, c1, lane, G + oG3 + (size_t)m * 32 * kOutPad, kOutPad);
   }
 }
 
 int train_splits(int rows) {
-  const int s = (rows + 511) / 512;
+  const int s = (rows + 255) / 256;
   return s < 1 ? 1 : (s > kMaxSplits ? kMaxSplits : s);
 }
 

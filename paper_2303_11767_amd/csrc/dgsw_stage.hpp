@@ -8,7 +8,7 @@
 //
 // One fused kernel per Runge-Kutta stage.  Work unit: one element, handled by
 // NP = r+1 lanes ("line lanes"); a 64-lane wavefront holds 64/NP elements and
-// is one workgroup.  Lane t of an element owns line t of the element's data in
+// works on its own.  Lane t of an element owns line t of the element's data in
 // every phase and the phases are joined by transposes through LDS:
 //
 //   load      lane t holds modal row b = t of h, hu, hv (n contiguous values:
@@ -143,8 +143,7 @@ __device__ __forceinline__ double dg_sqrt<double>(double x) {
 template <>
 __device__ __forceinline__ float dg_sqrt<float>(float x) { return __builtin_amdgcn_sqrtf(x); }
 
-// LDS ordering between the lanes of one wavefront (a workgroup is one
-// wavefront): LDS requests of a wave complete in order, so a wave-scope fence
+// LDS ordering between the lanes of one wavefront: LDS requests of a wave complete in order, so a wave-scope fence
 // around a scheduling barrier is enough.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
