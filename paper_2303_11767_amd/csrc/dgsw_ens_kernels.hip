@@ -6,22 +6,26 @@
 namespace dgsw {
 
 // ------------------------------------------------------------------ ensemble
-// LDS of one wavefront for any order up to NPMAX
 // strips where the mesh kernel takes them at any size
 template <typename T, int NP>
 constexpr bool ens_strips = Shape<T, NP>::UNALIGNED && sizeof(T) == 4;
+// LDS of one wavefront for any order up to NPMAX (the fused kernel)
 template <typename T, int NPMAX>
 struct LdsMax {
   using S_ = Shape<T, NPMAX>;
   static constexpr int tab = S_::cmax(S_::TB, LdsMax<T, NPMAX - 1>::tab);
-  static constexpr int sh = S_::cmax(S_::wave(ens_strips<T, NPMAX>), LdsMax<T, NPMAX - 1>::sh);
+  static constexpr int sh = S_::cmax(S_::wave(false), LdsMax<T, NPMAX - 1>::sh);
 };
 template <typename T>
 struct LdsMax<T, 0> {
   static constexpr int tab = 0, sh = 0;
 };
 
-template <typename T, int NP, int CM>
+// FUSED: the kernel over all orders, at the union of their registers; strips and
+// freely moved table loads, which pay in the kernels of one order, cost it a
+// wavefront per SIMD and a hundred spilled scalars (64 FP32 members 1.75 -> 2.4 ms
+// a step)
+template <typename T, int NP, int CM, bool FUSED>
 __device__ __forceinline__ void ens_case(const EnsItem &m, const unsigned char *__restrict__ tabs, const T *q,
                                          const T *q0, T *out, int combine, T c0, T ce, int lane, T *tab, T *sh) {
   StageArgs<T, NP> A;
@@ -42,7 +46,8 @@ __device__ __forceinline__ void ens_case(const EnsItem &m, const unsigned char *
   A.c1 = T(0);
   A.ce = ce;
   A.dt = T(m.dt);
-  stage_wave<T, NP, CM, ens_strips<T, NP>>(A, m.j, m.seg, lane, tab, sh);
+  constexpr bool ST = !FUSED && ens_strips<T, NP>;
+  stage_wave<T, NP, CM, ST, !FUSED && (ST || sizeof(T) == 4)>(A, m.j, m.seg, lane, tab, sh);
 }
 
 // One launch per Runge-Kutta stage for a whole ensemble of meshes of different
@@ -53,7 +58,8 @@ __device__ __forceinline__ void ens_case(const EnsItem &m, const unsigned char *
 // its WPB wavefronts take every WPB-th item.  The order of each member is a
 // wave-uniform switch.
 template <typename T, int NPMAX, int WPB, int CM>
-__global__ __launch_bounds__(64 * WPB) void k_ens_stage(const T *__restrict__ q, const T *q0, T *out,
+__global__ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && NPMAX <= 5 && WPB == 4 ? 3 : 1)))   // one register over otherwise
+__launch_bounds__(64 * WPB) void k_ens_stage(const T *__restrict__ q, const T *q0, T *out,
                                                         const unsigned char *__restrict__ tabs,
                                                         const EnsItem *__restrict__ items,
                                                         const int *__restrict__ bounds, int combine,
@@ -67,17 +73,17 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage(const T *__restrict__ q,
   for (int it = bounds[part] + wv; it < end; it += WPB) {
     const EnsItem m = items[it];
     switch (m.np) {
-      case 1: ens_case<T, 1, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 2: ens_case<T, 2, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 3: ens_case<T, 3, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 4: ens_case<T, 4, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 5: ens_case<T, 5, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 1: ens_case<T, 1, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 2: ens_case<T, 2, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 3: ens_case<T, 3, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 4: ens_case<T, 4, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 5: ens_case<T, 5, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
       default:
         if constexpr (NPMAX > 5) {
           switch (m.np) {
-            case 6: ens_case<T, (NPMAX > 5 ? 6 : 1), CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-            case 7: ens_case<T, (NPMAX > 6 ? 7 : 1), CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-            case 8: ens_case<T, (NPMAX > 7 ? 8 : 1), CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+            case 6: ens_case<T, (NPMAX > 5 ? 6 : 1), CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+            case 7: ens_case<T, (NPMAX > 6 ? 7 : 1), CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+            case 8: ens_case<T, (NPMAX > 7 ? 8 : 1), CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
             default: break;
           }
         }
@@ -128,7 +134,7 @@ template <typename T, int NP, int LAY, int CM>
 __device__ __forceinline__ void ens_item(const EnsItem &m, const unsigned char *__restrict__ tabs, const T *q,
                                          const T *q0, T *out, int combine, T c0, T ce, int lane, T *tab, T *sh) {
   if constexpr (LAY == 0) {
-    ens_case<T, NP, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh);
+    ens_case<T, NP, CM, false>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh);
   } else if constexpr (M4<T, NP>) {
     const StageArgs<T, NP> A = ens_args<T, NP>(m, tabs, q, q0, out, combine, c0, ce);
     m4_run<CM, false>(

@@ -343,7 +343,7 @@ __device__ __forceinline__ void strip_epilogue(const StageArgs<T, NP> &A, int co
 // take 0 or 1 from A.combine (the ensemble kernels).
 constexpr int CM_RUNTIME = 3;
 
-template <typename T, int NP, int CM, bool STRIPS>
+template <typename T, int NP, int CM, bool STRIPS, bool CAS = STRIPS || sizeof(T) == 4>
 __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int j, const int seg,
                                            const int lane, T *tab, T *sh) {
   using S_ = Shape<T, NP>;
@@ -352,10 +352,9 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   const T *q0 = A.q0;
   T *out = A.out;
   const T *__restrict__ forcing = A.forcing;
-  // the tables, never written while a stage runs; with strips and in FP32 in the
-  // constant address space, whose uniform loads are scalar ones also behind the
-  // loads into LDS, and may be moved freely (r = 3 FP32 720x360 38.2 -> 35.7 us)
-  constexpr bool CAS = STRIPS || sizeof(T) == 4;
+  // CAS: the tables, never written while a stage runs, in the constant address
+  // space, whose uniform loads are scalar ones also behind the loads into LDS, and
+  // may be moved freely (r = 3 FP32 720x360 38.2 -> 35.7 us): with strips and in FP32
   using GT_ = const GlobTab<T, NP>;
   using RT_ = const RowTab<T, NP>;
   using glob_p = typename std::conditional<CAS, __attribute__((address_space(4))) GT_ *, GT_ *>::type;
