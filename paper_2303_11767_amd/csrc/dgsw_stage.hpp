@@ -302,7 +302,7 @@ template <typename T, int NP, int MAXV, bool FULL>
 __device__ __forceinline__ void strip_epilogue(const StageArgs<T, NP> &A, int combine, bool use_q0, size_t base,
                                                int nv, const T *sh, int lane) {
   constexpr int VL = (MAXV + 63) / 64;
-  const T *__restrict__ q = A.q + base, *__restrict__ f = A.forcing ? A.forcing + base : nullptr;
+  const T *__restrict__ q = A.q + base;
   const T *q0 = A.q0 + base, *qa = A.qa + base, *qb = A.qb + base;
   T *out = A.out + base;
   T qv[VL], q0v[VL], xa[VL], xb[VL];
@@ -327,9 +327,7 @@ __device__ __forceinline__ void strip_epilogue(const StageArgs<T, NP> &A, int co
   }
 #pragma unroll
   for (int k = 0; k < VL; ++k) {
-    T acc = sh[at(k)];
-    if (f) acc += f[at(k)];
-    const T r = stage_combine<T>(acc, qv[k], q0v[k], xa[k], xb[k], combine, A);
+    const T r = stage_combine<T>(sh[at(k)], qv[k], q0v[k], xa[k], xb[k], combine, A);
     if ((FULL && 64 * (k + 1) <= MAXV) || 64 * k + lane < nv) out[64 * k + lane] = r;
   }
 }
@@ -659,10 +657,20 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
       XW += S[6 * NP * NP + (v * 2 + 1) * NP + p] * bmt[p];
     }
     const T cXE = cF * XE, cXW = cF * XW;
+    if constexpr (STRIPS) {
+      // as a row, so that both forms add the same terms in the same order (a mesh's
+      // layers take strips only where there are enough of them)
+      if (forcing) {
+        load_row<T, NP>(forcing + base + v * N, fr[v]);
+      } else {
+#pragma unroll
+        for (int a = 0; a < NP; ++a) fr[v][a] = T(0);
+      }
+    }
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
       // the forcing, then chained FMAs (a sum of products first costs a third instruction)
-      T acc = STRIPS ? T(0) : fr[v][a];
+      T acc = fr[v][a];
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
         acc += gt->D[p][a] * zd[p];
