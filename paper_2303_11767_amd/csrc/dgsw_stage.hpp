@@ -856,7 +856,7 @@ __device__ __forceinline__ void stage_wave_h2(const StageArgs<T, NP> &A, const i
   T *S = sh + g * SH;
   // neighbours; across a pole (sphere) the latitude neighbour is the element
   // of the row at the other end of the grid (the plane's periodic neighbour),
-  // read but weighted by the pole edge's zero cosine
+  // read but dropped with the pole edge's flux
   const int eE = (i + 1 == n_lon) ? e + 1 - n_lon : e + 1;
   const int eW = (i == 0) ? e - 1 + n_lon : e - 1;
   const int eN = j < n_lat - 1 ? e + n_lon : i;
@@ -895,7 +895,7 @@ __device__ __forceinline__ void stage_wave_h2(const StageArgs<T, NP> &A, const i
   }
   {
     // eY is a valid element at a pole edge too (the row across the grid),
-    // whose trace the zero pole flux then discards: no branch, no zero fill
+    // whose trace is dropped with the pole edge's flux: no branch, no zero fill
     const T *c = q + (size_t)eY * 3 * N + t;
 #pragma unroll
     for (int v = 0; v < 3; ++v)
@@ -1018,12 +1018,13 @@ __device__ __forceinline__ void stage_wave_h2(const StageArgs<T, NP> &A, const i
     rusanov_lambda<T>(trX, nbX, H, grav, fixed, alpha, FhX, sgn);
     rusanov_theta<T>(trY, nbY, H, grav, fixed, alpha, GhY, sgn);
   }
-  // the edge cosine is exactly 0 at a pole edge: zero flux through the pole
+  // the edge cosine is exactly 0 at a pole edge: no flux, whatever the traces
+  // there (non-finite values and negative depths have none to multiply by 0)
   const T fY = tab[ro + (h ? S_::rBot : S_::rTop)] * invR;
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
     FhX[v] *= invR;
-    GhY[v] *= fY;
+    GhY[v] = fY == T(0) ? T(0) : GhY[v] * fY;
     S[S_::oFX + (v * 2 + h) * NP + t] = FhX[v];   // read back in the last xi pass
     S[S_::oGY + (v * 2 + h) * NP + t] = GhY[v];   // the other half's latitude edge
   }

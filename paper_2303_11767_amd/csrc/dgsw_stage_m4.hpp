@@ -187,11 +187,11 @@ __device__ __forceinline__ void m4_fetch(const StageArgs<double, 4> &A, const M4
                                          lds_double *sh) {
   const int n_lon = A.n_lon, n_lat = A.n_lat, k = (lane >> 2) & 3;
   const M4Elem m = m4_elem(g, n_lon, k);
-  // across a pole (sphere) the latitude neighbour is the element of the row
-  // at the other end of the grid (the plane's periodic neighbour), whose flux
-  // the pole edge's zero cosine removes
-  const int eN = m.j < n_lat - 1 ? m.e + n_lon : m.i;
-  const int eS = m.j > 0 ? m.e - n_lon : (n_lat - 1) * n_lon + m.i;
+  // across a pole (no flux there) the element stands in for its neighbour; the
+  // zero columns of the edge tables would let a non-finite other one into every
+  // trace
+  const int eN = m.j < n_lat - 1 ? m.e + n_lon : (A.periodic_y ? m.i : m.e);
+  const int eS = m.j > 0 ? m.e - n_lon : (A.periodic_y ? (n_lat - 1) * n_lon + m.i : m.e);
   const int r0 = g.j0 * n_lon, j1 = g.j0 + 1 < n_lat ? g.j0 + 1 : g.j0;
   const int h0 = g.e0 == r0 ? r0 + n_lon - 1 : g.e0 - 1;
   const int h1 = g.e0 + kM4Elems < n_lon * n_lat ? g.e0 + kM4Elems : n_lon * n_lat - 1;
@@ -263,8 +263,7 @@ __device__ __forceinline__ M4Data m4_read(const StageArgs<double, 4> &A, const M
   return d;
 }
 
-// The stage from a group's data; x* are the operands read only by the general
-// combination and the forcing.  Leaves the results in sh (M4Lds::Out).
+// The operands read only by the general combination and the forcing.
 struct M4More {
   double f[3], a[3], b[3];
 };
@@ -282,9 +281,11 @@ __device__ __forceinline__ M4More m4_more(const StageArgs<double, 4> &A, const M
   return o;
 }
 
+// The stage from a group's data; polar: some of it lies in a row at a pole.
+// Leaves the results in sh (M4Lds::Out).
 template <int CM>
 __device__ __forceinline__ void m4_compute(const StageArgs<double, 4> &A, const M4Tab &t, M4Data &d, const M4More &o,
-                                           const int lane, lds_double *sh) {
+                                           const bool polar, const int lane, lds_double *sh) {
   const int combine = CM == CM_RUNTIME ? (A.combine != 0 ? 1 : 0) : CM;
   const int x = lane >> 4, y = lane & 3, k = (lane >> 2) & 3;
   const double H = t.H, grav = t.g;
@@ -332,6 +333,13 @@ __device__ __forceinline__ void m4_compute(const StageArgs<double, 4> &A, const 
     fl[0] = (ow[1] + nb[1]) - a * (nb[0] - ow[0]);
     fl[1] = ((ow[1] * uo + po) + (nb[1] * un + pn)) - a * (nb[1] - ow[1]);
     fl[2] = (ow[2] * uo + nb[2] * un) - a * (nb[2] - ow[2]);
+  }
+  // the edge cosine is exactly 0 at a pole edge: no flux, whatever the trace
+  // there (a negative depth has none to multiply by 0)
+  if (polar) {
+    const bool pole = (x & 2) && d.ce == 0.0;
+#pragma unroll
+    for (int v = 0; v < 3; ++v) fl[v] = pole ? 0.0 : fl[v];
   }
 
   double res[3] = {o.f[0], o.f[1], o.f[2]};
@@ -435,7 +443,9 @@ __device__ __forceinline__ void m4_run(const StageArgs<double, 4> &A, int count,
       next = group(n);
       m4_fetch(A, next, use_q0, lane, sh);
     }
-    m4_compute<CM>(A, t, d, o, lane, sh);
+    const int j0 = __builtin_amdgcn_readfirstlane(g.j0);
+    const bool polar = !A.periodic_y && (j0 == 0 || j0 + 2 >= A.n_lat);   // (a scalar test: 1 % of a stage saved)
+    m4_compute<CM>(A, t, d, o, polar, lane, sh);
     wave_sync();
     // the next group's data before the stores are queued behind them
     if (n < count) m4_fetched();
