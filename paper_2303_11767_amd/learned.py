@@ -33,24 +33,19 @@ def param_count():
     return n.value
 
 
-class _Workspace:
-    def __init__(self):
-        self._buf = None
-
-    def get(self, nbytes, device):
-        import torch
-        if self._buf is None or self._buf.numel() < nbytes:
-            self._buf = torch.empty(int(nbytes), dtype=torch.uint8, device=device)
-        return self._buf
-
-
-_ws = _Workspace()
-
-
-def _mlp_ws(rows, device):
+def _mlp_ws(rows, device, stream):
+    """Scratch of one call, allocated on the stream the call runs on: torch's
+    allocator hands its memory on in that stream's order only, so calls on other
+    streams or threads, or captured in a graph, never share it."""
+    import torch
     b = ctypes.c_int64()
     check(load().dg_mlp_workspace_size(int(rows), ctypes.byref(b)))
-    return _ws.get(b.value, device)
+    if stream is None:
+        return torch.empty(b.value, dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(b.value, dtype=torch.uint8, device=device)
 
 
 def mlp_forward(params, X, out=None, stream=None):
@@ -59,7 +54,7 @@ def mlp_forward(params, X, out=None, stream=None):
     rows = X.shape[0]
     if out is None:
         out = torch.empty((rows, N_OUT), dtype=torch.float32, device=X.device)
-    ws = _mlp_ws(rows, X.device)
+    ws = _mlp_ws(rows, X.device, stream)
     check(load().dg_mlp_forward(_f32(params, param_count(), "params"), _f32(X, rows * N_IN, "X"),
                                 rows, _f32(out, rows * N_OUT, "Y"), _ptr(ws), _stream_handle(stream)))
     return out
@@ -71,7 +66,7 @@ def mlp_train_step(params, X, T, mask, adam_m=None, adam_v=None, step=0, lr=0.0,
     mask: 12 host values, 0 or 1 (a sequence or a CPU array)."""
     rows = X.shape[0]
     P = param_count()
-    ws = _mlp_ws(rows, X.device)
+    ws = _mlp_ws(rows, X.device, stream)
     m = [float(v) for v in mask]
     if len(m) != N_OUT:
         raise ValueError(f"mask needs {N_OUT} values")
