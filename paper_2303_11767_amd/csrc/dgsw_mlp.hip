@@ -1078,18 +1078,42 @@ hipError_t launch_learned_out(int dtype, const LearnedOut &a, hipStream_t s) {
 // the matrix comes through the scalar cache.  64 800 FP64 elements, r = 4 to 1,
 // 45 MB: 10.3 us with one output per thread, now 8.3 us (with a
 // loop of runtime length, one load in flight per thread, 11.5 us).
-template <typename T, int NP>
+// STAGED: the values that are used come through LDS, read in memory order.  A
+// thread's own reads, nk values of every row, go over each cache line several
+// times, which costs most where rows are short and little of them is used: up
+// to half of it in FP32 and a fifth in FP64 (us for 720x360 elements, direct /
+// staged / one output per thread: FP32 r = 7 to 1 73.7 / 32.3 / 36.4, 7 to 3 50.6 /
+// 43.4 / 79.7, 4 to 1 22.7 / 17.1 / 19.6, FP64 6 to 0 61.4 / 51.7 / 68.9); otherwise
+// direct is as fast or faster (FP32 2 to 1 9.2 / 12.9, FP64 7 to 1 75.7 / 82.4).
+template <typename T, int NP, bool STAGED>
 __global__ __launch_bounds__(256) void k_project(const T *__restrict__ q, int n_lon, int nk, int bpr,
                                                  const double *__restrict__ P, T *__restrict__ out) {
   const int j = blockIdx.x / bpr;
-  const int t = (blockIdx.x - j * bpr) * 256 + threadIdx.x;
-  if (t >= n_lon * 3 * nk) return;
-  const int ev = t / nk, a = t - ev * nk;                  // (element of the row, variable), a
+  const int t0 = (blockIdx.x - j * bpr) * 256, t = t0 + threadIdx.x, all = n_lon * 3 * nk;
   const size_t row = (size_t)j * n_lon * 3;
-  const T *qe = q + (row + ev) * (NP * NP) + a;
+  const int ev0 = t0 / nk;                                 // the block's first (element of the row, variable)
+  // 256 threads cover at most 256 / nk + 2 of them, nk NP values each
+  __shared__ T sx[STAGED ? (256 + 2 * NP) * NP : 1];
+  if constexpr (STAGED) {
+    const int ev1 = (t0 + 255 < all ? t0 + 255 : all - 1) / nk, used = nk * NP, count = (ev1 - ev0 + 1) * used;
+    const T *src = q + (row + ev0) * (NP * NP);
+    for (int k = threadIdx.x; k < count; k += 256) {
+      const int ev = k / used, r = k - ev * used, b = r / nk;
+      sx[k] = src[ev * (NP * NP) + b * NP + (r - b * nk)];
+    }
+    __syncthreads();
+  }
+  if (t >= all) return;
+  const int ev = t / nk, a = t - ev * nk;                  // (element of the row, variable), a
   T x[NP];
+  if constexpr (STAGED) {
 #pragma unroll
-  for (int b = 0; b < NP; ++b) x[b] = a < NP ? qe[b * NP] : (T)0;
+    for (int b = 0; b < NP; ++b) x[b] = sx[((ev - ev0) * NP + b) * nk + a];
+  } else {
+    const T *qe = q + (row + ev) * (NP * NP) + a;
+#pragma unroll
+    for (int b = 0; b < NP; ++b) x[b] = a < NP ? qe[b * NP] : (T)0;
+  }
   const double *Pj = P + (size_t)j * nk * NP;
   T *o = out + (row + ev) * nk * nk + a;
   for (int bp = 0; bp < nk; ++bp) {
@@ -1105,9 +1129,18 @@ static hipError_t launch_project_t(const T *q, int n_lon, int n_lat, int np, int
                                    hipStream_t s) {
   const int bpr = (int)(((long long)n_lon * 3 * nk + 255) / 256);
   const dim3 grid((unsigned)((long long)bpr * n_lat)), block(256);
+  constexpr int kPart = sizeof(T) == 4 ? 2 : 5;
+  const bool staged = nk * kPart <= np;
   switch (np) {
-#define DGSW_PROJECT(NP) \
-  case NP: hipLaunchKernelGGL((k_project<T, NP>), grid, block, 0, s, q, n_lon, nk, bpr, P, out); break
+#define DGSW_PROJECT(NP)                                                                               \
+  case NP:                                                                                             \
+    if constexpr (NP >= kPart)                                                                         \
+      if (staged) {                                                                                    \
+        hipLaunchKernelGGL((k_project<T, NP, true>), grid, block, 0, s, q, n_lon, nk, bpr, P, out);    \
+        break;                                                                                         \
+      }                                                                                                \
+    hipLaunchKernelGGL((k_project<T, NP, false>), grid, block, 0, s, q, n_lon, nk, bpr, P, out);       \
+    break
     DGSW_PROJECT(1); DGSW_PROJECT(2); DGSW_PROJECT(3); DGSW_PROJECT(4);
     DGSW_PROJECT(5); DGSW_PROJECT(6); DGSW_PROJECT(7); DGSW_PROJECT(8);
 #undef DGSW_PROJECT
