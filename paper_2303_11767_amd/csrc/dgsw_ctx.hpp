@@ -19,7 +19,7 @@ struct dg_ctx {
   double *d_mass_w = nullptr;  // mass diagnostic weights [n_lat][np]
   double *d_partial = nullptr; // mass partial sums
   // mass result: pinned host memory the last kernel writes itself (a copy to
-  // pageable memory after it cost 8 us more a call)
+  // pageable memory after it cost 8 us more a call), taken with the first dg_mass
   double *h_out4 = nullptr;
   const void *forcing = nullptr;
   double min_width = 0.0;
