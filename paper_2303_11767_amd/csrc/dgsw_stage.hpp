@@ -656,17 +656,24 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
       XE += S[6 * NP * NP + (v * 2 + 0) * NP + p] * bmt[p];
       XW += S[6 * NP * NP + (v * 2 + 1) * NP + p] * bmt[p];
     }
-    const T cXE = cF * XE, cXW = cF * XW;
-    if constexpr (STRIPS) {
+    // rows: the general combination's two extra operands (combine == 2, classical
+    // RK4), one variable at a time, ahead of the sums (after them r = 4 FP64 needs
+    // more than 256 registers: one wavefront per SIMD, 180x90 20.8 us for 17.0)
+    T xa[NP], xb[NP];
+#pragma unroll
+    for (int a = 0; a < NP; ++a) xa[a] = xb[a] = T(0);
+    if constexpr (!STRIPS) {
+      if (combine == 2 && A.qa) load_row<T, NP>(A.qa + base + v * N, xa);
+      if (combine == 2 && A.qb) load_row<T, NP>(A.qb + base + v * N, xb);
+    } else if (forcing) {
       // as a row, so that both forms add the same terms in the same order (a mesh's
       // layers take strips only where there are enough of them)
-      if (forcing) {
-        load_row<T, NP>(forcing + base + v * N, fr[v]);
-      } else {
+      load_row<T, NP>(forcing + base + v * N, fr[v]);
+    } else {
 #pragma unroll
-        for (int a = 0; a < NP; ++a) fr[v][a] = T(0);
-      }
+      for (int a = 0; a < NP; ++a) fr[v][a] = T(0);
     }
+    const T cXE = cF * XE, cXW = cF * XW;
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
       // the forcing, then chained FMAs (a sum of products first costs a third instruction)
@@ -678,21 +685,9 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
       }
       acc -= gt->Pp[a] * cXE;
       acc += gt->Pm[a] * cXW;
-      res[v][a] = acc;
+      res[v][a] = STRIPS ? acc : stage_combine<T>(acc, qr[v][a], q0r[v][a], xa[a], xb[a], combine, A);
     }
-    if constexpr (!STRIPS) {
-      // general combination (combine == 2, classical RK4): its two extra
-      // operands, loaded one variable at a time
-      T xa[NP], xb[NP];
-#pragma unroll
-      for (int a = 0; a < NP; ++a) xa[a] = xb[a] = T(0);
-      if (combine == 2 && A.qa) load_row<T, NP>(A.qa + base + v * N, xa);
-      if (combine == 2 && A.qb) load_row<T, NP>(A.qb + base + v * N, xb);
-#pragma unroll
-      for (int a = 0; a < NP; ++a)
-        res[v][a] = stage_combine<T>(res[v][a], qr[v][a], q0r[v][a], xa[a], xb[a], combine, A);
-      if (active) store_row<T, NP>(out + base + v * N, res[v]);
-    }
+    if (!STRIPS && active) store_row<T, NP>(out + base + v * N, res[v]);
   }
   if constexpr (STRIPS) {
     wave_sync();
