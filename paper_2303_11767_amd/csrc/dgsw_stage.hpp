@@ -59,12 +59,15 @@ namespace dgsw {
 // fewest bank conflicts over the stage's accesses among those up to 28 values
 // (r = 1, whose unpadded stride makes most of its LDS accesses wait eight times:
 // stage times before and after at 720x360, FP64 half 29.9 / 23.5 us and line 36.8 /
-// 27.4, FP32 18.0 / 14.6 and 19.2 / 13.5; other orders within 2 %).
+// 27.4, FP32 18.0 / 14.6 and 19.2 / 13.5; other orders within 2 %).  0: none (the
+// half layout of r = 3 FP64 is the matrix-core stage of dgsw_stage_m4.hpp).
 template <typename T>
 constexpr int lds_stride(int np, int used, bool half) {
   constexpr int line32[9] = {0, 21, 50, 81, 120, 185, 266, 347, 436}, line64[9] = {0, 21, 50, 81, 122, 185, 260, 340, 434};
-  constexpr int half32[9] = {0, 22, 52, 101, 152, 217, 298, 392, 492}, half64[9] = {0, 22, 52, 92, 120, 217, 264, 392, 434};
-  return np > 8 ? used : (sizeof(T) == 4 ? (half ? half32[np] : line32[np]) : (half ? half64[np] : line64[np]));
+  constexpr int half32[9] = {0, 22, 52, 101, 152, 217, 298, 392, 492}, half64[9] = {0, 22, 52, 92, 0, 217, 264, 392, 434};
+  const int padded =
+      np > 8 ? 0 : (sizeof(T) == 4 ? (half ? half32[np] : line32[np]) : (half ? half64[np] : line64[np]));
+  return padded ? padded : used;
 }
 
 template <typename T, int NP>
@@ -337,10 +340,7 @@ __device__ __forceinline__ void strip_epilogue(const StageArgs<T, NP> &A, int co
 // loads) and the pole tests are uniform branches.  tab and sh are this
 // wavefront's LDS slices (TB and (GPW+1)*SH values).
 // CM: the stage combination as a compile-time mode (0: dq/dt, 1: Shu-Osher,
-// 2: general) so each launch carries only its own epilogue, or CM_RUNTIME to
-// take 0 or 1 from A.combine (the ensemble kernels).
-constexpr int CM_RUNTIME = 3;
-
+// 2: general) so each launch carries only its own epilogue.
 template <typename T, int NP, int CM, bool STRIPS, bool CAS = STRIPS || sizeof(T) == 4>
 __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int j, const int seg,
                                            const int lane, T *tab, T *sh) {
@@ -359,7 +359,7 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   using row_p = typename std::conditional<CAS, __attribute__((address_space(4))) RT_ *, RT_ *>::type;
   const glob_p gt = (glob_p)A.gt;
   const int n_lon = A.n_lon, n_lat = A.n_lat;
-  const int combine = CM == CM_RUNTIME ? (A.combine != 0 ? 1 : 0) : CM;
+  constexpr int combine = CM;
   const T c0 = A.c0, c1 = A.c1, dt = A.dt;
   int g = lane / NP, t = lane - g * NP;
   const bool idle = g >= GPW;          // the 64 mod NP spare lanes: a dummy LDS slot
@@ -728,7 +728,7 @@ struct ShapeH2 {
   // SPLIT: each half evaluates the node terms at its own NP / 2 nodes of a
   // column and hands them to the other half (FP64 with an even r + 1 >= 6; at
   // r = 3 the half layout is the matrix-core stage of dgsw_stage_m4.hpp)
-  static constexpr bool SPLIT = sizeof(T) == 8 && NP % 2 == 0 && NP >= 4;
+  static constexpr bool SPLIT = sizeof(T) == 8 && NP % 2 == 0 && NP >= 6;
   // second phase: the volume outputs [3][2][NP][NP], the longitude edge
   // fluxes of both halves [3][2][NP], and the latitude ones [3][2][NP] (oGY).
   // With SPLIT the latitude ones and then the node terms, XQ quantities
@@ -832,7 +832,7 @@ __device__ __forceinline__ void stage_wave_h2(const StageArgs<T, NP> &A, const i
   const T *__restrict__ forcing = A.forcing;
   const GlobTab<T, NP> *__restrict__ gt = A.gt;
   const int n_lon = A.n_lon, n_lat = A.n_lat;
-  const int combine = CM == CM_RUNTIME ? (A.combine != 0 ? 1 : 0) : CM;
+  constexpr int combine = CM;
   const T c0 = A.c0, c1 = A.c1, dt = A.dt;
   int g = lane / (2 * NP), r = lane - g * 2 * NP;
   const bool idle = g >= GPW;

@@ -286,7 +286,7 @@ __device__ __forceinline__ M4More m4_more(const StageArgs<double, 4> &A, const M
 template <int CM>
 __device__ __forceinline__ void m4_compute(const StageArgs<double, 4> &A, const M4Tab &t, M4Data &d, const M4More &o,
                                            const bool polar, const int lane, lds_double *sh) {
-  const int combine = CM == CM_RUNTIME ? (A.combine != 0 ? 1 : 0) : CM;
+  constexpr int combine = CM;
   const int x = lane >> 4, y = lane & 3, k = (lane >> 2) & 3;
   const double H = t.H, grav = t.g;
   const double hq = d.Q[0] - t.h2;
