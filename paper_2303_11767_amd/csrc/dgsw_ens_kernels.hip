@@ -6,26 +6,45 @@
 namespace dgsw {
 
 // ------------------------------------------------------------------ ensemble
-// strips where the mesh kernel takes them at any size
-template <typename T, int NP>
-constexpr bool ens_strips = Shape<T, NP>::UNALIGNED && sizeof(T) == 4;
+// What a line stage takes in the kernel over all orders (kFused), the persistent
+// kernel of one order and the flat one.  An item is short and comes with loads of
+// its own, so strips and freely moved table loads pay less often than in a mesh.
+// Microseconds a stage of 32 members 33x17 .. 180x90 and one of 360x180, FP32:
+//   strips / rows           r = 1        2            4            5            6
+//     flat              14.2 / 14.6  25.8 / 24.7  62.7 / 72.0  95.1 / 93.9  138.8 / 147.1
+//     persistent        14.3 / 14.3  28.9 / 27.3  84.1 / 82.4   122 / 113    164 / 154
+//   (8 members, r = 4 persistent with two wavefronts 20.0 / 19.8, r = 1 6.2 / 5.8)
+//   tables moved freely / in order: r = 5 flat 93.9 / 92.4, r = 7 flat 187 / 179,
+//     persistent 186 / 193
+// In the fused kernel both cost a wavefront per SIMD and a hundred spilled scalars
+// (64 members 1.75 -> 2.4 ms a step).
+enum { kFused, kPersistent, kFlat };
+template <typename T, int NP, int FORM>
+constexpr bool ens_strips = sizeof(T) == 4 && ((NP == 5 && FORM != kFused) || ((NP == 2 || NP == 7) && FORM == kFlat));
+template <typename T, int NP, int FORM>
+constexpr bool ens_moved = sizeof(T) == 4 && FORM != kFused && NP != 6 && !(NP == 8 && FORM == kFlat);
+// Wavefronts a SIMD: r = 6 FP32 in strips needs a few registers more than three
+// allow (148.4 -> 138.8 us; the persistent kernel would spill, 164 -> 221).  The
+// matrix-core items hold 113 .. 122 registers and 22 accumulation registers, so
+// three; held to four, flat items take 54.7 us for 55.2 and persistent ones spill
+// (81 for 73).
+template <typename T, int NP, int LAY>
+constexpr int ens_flat_waves = sizeof(T) == 4 && NP == 7 && LAY == 0 ? 3 : 1;
 // LDS of one wavefront for any order up to NPMAX (the fused kernel)
 template <typename T, int NPMAX>
 struct LdsMax {
   using S_ = Shape<T, NPMAX>;
   static constexpr int tab = S_::cmax(S_::TB, LdsMax<T, NPMAX - 1>::tab);
-  static constexpr int sh = S_::cmax(S_::wave(false), LdsMax<T, NPMAX - 1>::sh);
+  // (a wavefront's slice on 16 bytes: wide accesses at other addresses made this
+  // kernel 5 .. 12 % slower with several wavefronts a workgroup)
+  static constexpr int sh = S_::cmax((S_::wave(false) + 3) / 4 * 4, LdsMax<T, NPMAX - 1>::sh);
 };
 template <typename T>
 struct LdsMax<T, 0> {
   static constexpr int tab = 0, sh = 0;
 };
 
-// FUSED: the kernel over all orders, at the union of their registers; strips and
-// freely moved table loads, which pay in the kernels of one order, cost it a
-// wavefront per SIMD and a hundred spilled scalars (64 FP32 members 1.75 -> 2.4 ms
-// a step)
-template <typename T, int NP, int CM, bool FUSED>
+template <typename T, int NP, int CM, int FORM>
 __device__ __forceinline__ void ens_case(const EnsItem &m, const unsigned char *__restrict__ tabs, const T *q,
                                          const T *q0, T *out, int combine, T c0, T ce, int lane, T *tab, T *sh) {
   StageArgs<T, NP> A;
@@ -46,8 +65,7 @@ __device__ __forceinline__ void ens_case(const EnsItem &m, const unsigned char *
   A.c1 = T(0);
   A.ce = ce;
   A.dt = T(m.dt);
-  constexpr bool ST = !FUSED && ens_strips<T, NP>;
-  stage_wave<T, NP, CM, ST, !FUSED && (ST || sizeof(T) == 4)>(A, m.j, m.seg, lane, tab, sh);
+  stage_wave<T, NP, CM, ens_strips<T, NP, FORM>, ens_moved<T, NP, FORM>>(A, m.j, m.seg, lane, tab, sh);
 }
 
 // One launch per Runge-Kutta stage for a whole ensemble of meshes of different
@@ -73,17 +91,17 @@ __launch_bounds__(64 * WPB) void k_ens_stage(const T *__restrict__ q, const T *q
   for (int it = bounds[part] + wv; it < end; it += WPB) {
     const EnsItem m = items[it];
     switch (m.np) {
-      case 1: ens_case<T, 1, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 2: ens_case<T, 2, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 3: ens_case<T, 3, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 4: ens_case<T, 4, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-      case 5: ens_case<T, 5, CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 1: ens_case<T, 1, CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 2: ens_case<T, 2, CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 3: ens_case<T, 3, CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 4: ens_case<T, 4, CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+      case 5: ens_case<T, 5, CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
       default:
         if constexpr (NPMAX > 5) {
           switch (m.np) {
-            case 6: ens_case<T, (NPMAX > 5 ? 6 : 1), CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-            case 7: ens_case<T, (NPMAX > 6 ? 7 : 1), CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
-            case 8: ens_case<T, (NPMAX > 7 ? 8 : 1), CM, true>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+            case 6: ens_case<T, (NPMAX > 5 ? 6 : 1), CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+            case 7: ens_case<T, (NPMAX > 6 ? 7 : 1), CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
+            case 8: ens_case<T, (NPMAX > 7 ? 8 : 1), CM, kFused>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh); break;
             default: break;
           }
         }
@@ -120,21 +138,22 @@ __device__ __forceinline__ StageArgs<T, NP> ens_args(const EnsItem &m, const uns
   return A;
 }
 
-// LDS of one wavefront per layout: the line and half variants
-template <typename T, int NP, int LAY>
+// LDS of one wavefront per layout: the line and half variants, on 16 bytes
+template <typename T, int NP, int LAY, int FORM>
 struct EnsLds {
   static constexpr bool G4 = M4<T, NP> && LAY == 1;
   static constexpr int TB = G4 ? 2 : (LAY == 0 ? Shape<T, NP>::TB : ShapeH2<T, NP>::TB);
-  static constexpr int SH = G4 ? kM4Lds
-                               : (LAY == 0 ? Shape<T, NP>::wave(ens_strips<T, NP>)
-                                           : ShapeH2<T, NP>::SLOTS * ShapeH2<T, NP>::SH);
+  static constexpr int USED = G4 ? kM4Lds
+                                 : (LAY == 0 ? Shape<T, NP>::wave(ens_strips<T, NP, FORM>)
+                                             : ShapeH2<T, NP>::SLOTS * ShapeH2<T, NP>::SH);
+  static constexpr int SH = (USED + 3) / 4 * 4;
 };
 
-template <typename T, int NP, int LAY, int CM>
+template <typename T, int NP, int LAY, int CM, int FORM>
 __device__ __forceinline__ void ens_item(const EnsItem &m, const unsigned char *__restrict__ tabs, const T *q,
                                          const T *q0, T *out, int combine, T c0, T ce, int lane, T *tab, T *sh) {
   if constexpr (LAY == 0) {
-    ens_case<T, NP, CM, false>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh);
+    ens_case<T, NP, CM, FORM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab, sh);
   } else if constexpr (M4<T, NP>) {
     const StageArgs<T, NP> A = ens_args<T, NP>(m, tabs, q, q0, out, combine, c0, ce);
     m4_run<CM, false>(
@@ -161,14 +180,14 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage_np(const T *__restrict__
                                                            const EnsItem *__restrict__ items,
                                                            const int *__restrict__ bounds, int combine,
                                                            T c0, T ce) {
-  __shared__ T tab_all[WPB][EnsLds<T, NP, LAY>::TB];
-  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY>::SH];
+  __shared__ T tab_all[WPB][EnsLds<T, NP, LAY, kPersistent>::TB];
+  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY, kPersistent>::SH];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int part = xcd_block(blockIdx.x, gridDim.x);
   const int end = bounds[part + 1];
   for (int it = bounds[part] + wv; it < end; it += WPB) {
     const EnsItem m = items[it];
-    ens_item<T, NP, LAY, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab_all[wv], sh_all[wv]);
+    ens_item<T, NP, LAY, CM, kPersistent>(m, tabs, q, q0, out, combine, c0, ce, lane, tab_all[wv], sh_all[wv]);
   }
 }
 
@@ -176,17 +195,18 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage_np(const T *__restrict__
 // wavefront, so the hardware schedules the ensemble like an ordinary grid
 // (no loop: same register budget as the single-mesh kernel).
 template <typename T, int NP, int LAY, int WPB, int CM>
-__global__ __launch_bounds__(64 * WPB) void k_ens_stage_flat(const T *__restrict__ q, const T *q0, T *out,
+__global__ __attribute__((amdgpu_waves_per_eu(ens_flat_waves<T, NP, LAY>)))
+__launch_bounds__(64 * WPB) void k_ens_stage_flat(const T *__restrict__ q, const T *q0, T *out,
                                                              const unsigned char *__restrict__ tabs,
                                                              const EnsItem *__restrict__ items,
                                                              int begin, int end, int combine, T c0, T ce) {
-  __shared__ T tab_all[WPB][EnsLds<T, NP, LAY>::TB];
-  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY>::SH];
+  __shared__ T tab_all[WPB][EnsLds<T, NP, LAY, kFlat>::TB];
+  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY, kFlat>::SH];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int it = begin + xcd_block(blockIdx.x, gridDim.x) * WPB + wv;
   if (it >= end) return;
   const EnsItem m = items[it];
-  ens_item<T, NP, LAY, CM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab_all[wv], sh_all[wv]);
+  ens_item<T, NP, LAY, CM, kFlat>(m, tabs, q, q0, out, combine, c0, ce, lane, tab_all[wv], sh_all[wv]);
 }
 
 // the combination mode is a template parameter of the ensemble kernels too:
