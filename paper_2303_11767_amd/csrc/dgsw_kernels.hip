@@ -89,8 +89,12 @@ __launch_bounds__(64 * WPB) void k_dg_stage(StageArgs<T, NP> A, int segs) {
   const int lev = blk / per;
   blk -= lev * per;
   const int j = blk / segs;
-  stage_wave<T, NP, CM, STRIPS>(layer_args(A, lev), j, blk - j * segs, threadIdx.x & 63, tab_all[wv],
-                        sh_all[wv]);
+  // (r = 7 FP32, general combination: the tables' loads moved freely spill scalars,
+  // which costs where few wavefronts hide it, 64x32 9.5 -> 12.0 us a stage of RK4, and
+  // brings a second wavefront per SIMD where there are many, 720x360 352 -> 273)
+  constexpr bool MOVED = STRIPS || (sizeof(T) == 4 && !(NP == 8 && CM == 2 && WPB == 1));
+  stage_wave<T, NP, CM, STRIPS, MOVED>(layer_args(A, lev), j, blk - j * segs, threadIdx.x & 63, tab_all[wv],
+                                       sh_all[wv]);
 }
 
 // ------------------------------------------------------------------ mass
@@ -237,24 +241,25 @@ static hipError_t launch_stage_t(const StageLaunch &a, hipStream_t s) {
   constexpr int GPW = Shape<T, NP>::GPW;
   const int segs = (a.n_lon + GPW - 1) / GPW;
   const int waves = segs * a.n_lat * a.levels;
-  // Strips (rows that are not 16-byte aligned): in FP32 always, in FP64, where
-  // their LDS costs wavefronts, on meshes that fill the GPU several times.  Stage
-  // times, rows / strips, 720x360: r = 2 FP32 29.6 / 26.6 us, r = 4 94.9 / 69.0,
-  // r = 5 132 / 110, FP64 r = 2 62.4 / 52.0, r = 4 179 / 146; FP64 r = 2 360x180 (3240
-  // wavefronts) 18.2 / 18.9, r = 4 360x180 (5400) 48.1 / 43.5, 180x90 (1350) 15.5 /
-  // 15.8; rows that are aligned are faster as rows (r = 3 FP32 38.2 / 41.3).  One
-  // wavefront per workgroup then (their LDS, r = 5 FP32 720x360 134 us with four);
-  // with rows four on large meshes.
+  // Strips (rows that are not 16-byte aligned): in FP64, where their LDS costs
+  // wavefronts, on meshes that fill the GPU several times, in FP32 from where the
+  // trips through LDS are hidden by other wavefronts.  Stage times, rows / strips,
+  // 720x360: r = 2 FP32 29.6 / 26.6 us, r = 4 94.9 / 69.0, r = 5 132 / 110, FP64 r = 2
+  // 62.4 / 52.0, r = 4 179 / 146; FP64 r = 2 360x180 (3240 wavefronts) 18.2 / 18.9, r = 4
+  // 360x180 (5400) 48.1 / 43.5, 180x90 (1350) 15.5 / 15.8; FP32 64x32 r = 4 (192) 6.4 / 7.1,
+  // r = 6 (256) 8.9 / 9.8, 90x45 r = 4 (360) 7.5 / 7.6, r = 5 (405) 8.5 / 8.3, 120x60 r = 4
+  // (600) 8.4 / 7.8; rows that are aligned are faster as rows (r = 3 FP32 38.2 / 41.3), and
+  // the single values of r = 0 FP32 (6.0 / 6.3).  One wavefront per workgroup then
+  // (their LDS, r = 5 FP32 720x360 134 us with four); with rows four on large meshes.
   const bool big = waves >= 4096;
-  constexpr bool U = Shape<T, NP>::UNALIGNED;
+  constexpr bool U = Shape<T, NP>::UNALIGNED && !(sizeof(T) == 4 && NP == 1);
+  constexpr int strip_waves = sizeof(T) == 4 ? 384 : 4096;
 #define DGSW_LINE_K(W_, CM_, ST_) \
   hipLaunchKernelGGL((k_dg_stage<T, NP, W_, CM_, ST_>), dim3((waves + W_ - 1) / W_), dim3(64 * W_), 0, s, A, segs)
 #define DGSW_LINE(CM_)                                    \
   do {                                                    \
-    if constexpr (U && sizeof(T) == 4) {                  \
-      DGSW_LINE_K(1, CM_, true);                          \
-    } else if constexpr (U) {                             \
-      if (big) DGSW_LINE_K(1, CM_, true);                 \
+    if constexpr (U) {                                    \
+      if (waves >= strip_waves) DGSW_LINE_K(1, CM_, true); \
       else DGSW_LINE_K(1, CM_, false);                    \
     } else {                                              \
       if (big) DGSW_LINE_K(4, CM_, false);                \

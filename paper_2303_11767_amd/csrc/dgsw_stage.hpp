@@ -341,7 +341,7 @@ __device__ __forceinline__ void strip_epilogue(const StageArgs<T, NP> &A, int co
 // wavefront's LDS slices (TB and (GPW+1)*SH values).
 // CM: the stage combination as a compile-time mode (0: dq/dt, 1: Shu-Osher,
 // 2: general) so each launch carries only its own epilogue.
-template <typename T, int NP, int CM, bool STRIPS, bool CAS = STRIPS || sizeof(T) == 4>
+template <typename T, int NP, int CM, bool STRIPS, bool CAS>
 __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int j, const int seg,
                                            const int lane, T *tab, T *sh) {
   using S_ = Shape<T, NP>;
@@ -352,7 +352,8 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   const T *__restrict__ forcing = A.forcing;
   // CAS: the tables, never written while a stage runs, in the constant address
   // space, whose uniform loads are scalar ones also behind the loads into LDS, and
-  // may be moved freely (r = 3 FP32 720x360 38.2 -> 35.7 us): with strips and in FP32
+  // may be moved freely (r = 3 FP32 720x360 38.2 -> 35.7 us): with strips and, but for
+  // the cases that the callers name, in FP32
   using GT_ = const GlobTab<T, NP>;
   using RT_ = const RowTab<T, NP>;
   using glob_p = typename std::conditional<CAS, __attribute__((address_space(4))) GT_ *, GT_ *>::type;
