@@ -276,9 +276,11 @@ int dg_ens_set_schedule(dg_ens *ens, int32_t waves_per_group, int32_t groups, in
 int dg_ens_get_schedule(const dg_ens *ens, int32_t *waves_per_group, int32_t *groups,
                         int32_t *fused);
 /* Stage-kernel layout (DG_KERNEL_*, as dg_set_kernel) of every member of the
- * given order; at dg_ens_init the members of an order take the layout that a
- * single mesh of their total size would take.  DG_EINVAL if no member has that order, if
- * the schedule is the fused launch and kernel is not DG_KERNEL_LINE, or while
+ * given order; at dg_ens_init the members of an order take a layout by the size
+ * of all of them, the line layout where each member alone is large (over 512
+ * wavefronts of it at r >= 4, 2048 below; not at r = 1, nor in FP64 at r = 3 and
+ * from 5 on, where the half layout is the default).  DG_EINVAL if no member has that order,
+ * if the schedule is the fused launch and kernel is not DG_KERNEL_LINE, or while
  * graphs of the ensemble are live.  The schedule's settings are kept. */
 int dg_ens_set_kernel(dg_ens *ens, int32_t order, int32_t kernel);
 int dg_ens_get_kernel(const dg_ens *ens, int32_t order, int32_t *kernel);

@@ -158,6 +158,23 @@ int dgsw::default_layout(bool f64, int r, long long waves_line) {
 }
 
 namespace {
+constexpr long long kAlways = INT64_MAX;
+}
+// The same for the members of one order of an ensemble, which run in one launch: by
+// the wavefronts of all of them (microseconds a stage of 32 members up to 180x90
+// and one of 360x180, line / half: FP32 r = 2 24.7 / 36.9, r = 4 62 / 94, r = 5 92 / 99, r = 6
+// 139 / 201, r = 7 182 / 168, FP64 r = 2 45 / 49, r = 4 131 / 170, r = 5 327 / 206; eight
+// of them FP32 r = 3 9.7 / 9.5, FP64 r = 6 100 / 92).  The fused schedule runs the
+// line layout only, so orders whose members would take it each alone do, whatever
+// their sum: that schedule stays open to them without a dg_ens_set_kernel.
+int dgsw::default_ens_layout(bool f64, int r, long long waves_line, long long least_line) {
+  static constexpr long long few[2][kMaxNP] = {{2048, kAlways, 1024, kAlways, 512, kAlways, kAlways, kAlways},
+                                               {2048, 3072, 1024, 2048, 512, 1600, 512, kAlways}};
+  const bool line_alone = least_line > (r >= 4 ? 512 : 2048) && r != 1 && !(f64 && (r == 3 || r >= 5));
+  return line_alone || waves_line > few[f64 ? 0 : 1][r] ? DG_KERNEL_LINE : DG_KERNEL_HALF;
+}
+
+namespace {
 
 // Context from validated parameters and the host tables of its geometry.
 int make_ctx(const dg_mesh_desc *desc, const dgsw::HostTables &t, hipStream_t s, dg_ctx **out) {

@@ -39,5 +39,8 @@ namespace dgsw {
 int fail(int code, const std::string &msg);
 int hip_fail(hipError_t e, const char *what);
 bool aligned16(const void *p);
-int default_layout(bool f64, int order, long long waves_line);   // DG_KERNEL_LINE or DG_KERNEL_HALF
+// DG_KERNEL_LINE or DG_KERNEL_HALF for a mesh; for the members of one order of an
+// ensemble (wavefronts of the line layout: all members', the smallest one's)
+int default_layout(bool f64, int order, long long waves_line);
+int default_ens_layout(bool f64, int order, long long waves_line, long long least_line);
 }  // namespace dgsw

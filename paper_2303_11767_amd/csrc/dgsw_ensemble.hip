@@ -284,7 +284,7 @@ int dg_ens_init(const dg_mesh_desc *members, int32_t n_members, void *hip_stream
   e->elem_bytes = dtype == DG_F64 ? 8 : 4;
   const int64_t align = 16 / (int64_t)e->elem_bytes;
   e->off.assign(n_members + 1, 0);
-  long long waves_line[dgsw::kMaxNP] = {};
+  long long waves_line[dgsw::kMaxNP] = {}, least_line[dgsw::kMaxNP] = {};   // of an order: all members', the smallest's
   for (int m = 0; m < n_members; ++m) {
     dg_ctx *c = nullptr;
     int rc = dg_init_mesh(&members[m], hip_stream, &c);
@@ -296,14 +296,18 @@ int dg_ens_init(const dg_mesh_desc *members, int32_t n_members, void *hip_stream
     e->members.push_back(c);
     e->npmax = std::max(e->npmax, c->np);
     e->off[m + 1] = e->off[m] + (c->state_n + align - 1) / align * align;
-    waves_line[c->np - 1] += (long long)dgsw::waves_per_row(c->np, c->d.n_lon) * c->d.n_lat;
+    const long long w = (long long)dgsw::waves_per_row(c->np, c->d.n_lon) * c->d.n_lat;
+    long long &least = least_line[c->np - 1];
+    least = waves_line[c->np - 1] == 0 ? w : std::min(least, w);
+    waves_line[c->np - 1] += w;
   }
   // the members of an order run in one launch, so they take the layout of a mesh
   // with all of their wavefronts (by each member's own size, small members kept
   // the half layout: FP32 ensembles of 64 / 16 / 6 members 1003 / 295 / 161 us a
   // step against 918 / 248 / 130, 24 in FP64 771 against 729)
   for (const dg_ctx *c : e->members)
-    e->layout.push_back(dgsw::default_layout(e->dtype == 0, c->d.order, waves_line[c->np - 1]));
+    e->layout.push_back(
+        dgsw::default_ens_layout(e->dtype == 0, c->d.order, waves_line[c->np - 1], least_line[c->np - 1]));
   e->dt.assign(n_members, 0.0);
   if (e->off[n_members] >= (int64_t(1) << 31)) {
     ens_release(e);
