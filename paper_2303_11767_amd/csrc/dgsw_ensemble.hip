@@ -547,8 +547,9 @@ int dg_ens_autotune(dg_ens *ens, const void *q, void *work, const char *cache_pa
     *out_ms = t_best;
     return DG_OK;
   };
-  // 1. the layout of each order (flat per-order launches, 4 wavefronts per
-  //    workgroup), one order at a time with the others unchanged
+  // 1. the layout of each order (flat per-order launches, one wavefront per
+  //    workgroup: the default, and with four the line layout's strips look slower
+  //    than they then run), one order at a time with the others unchanged
   std::vector<int> lay(dgsw::kMaxNP, DG_KERNEL_LINE);
   for (int m = 0; m < ens->n; ++m) lay[ens->members[m]->np - 1] = ens->layout[m];
   for (int o : orders) {
@@ -557,7 +558,7 @@ int dg_ens_autotune(dg_ens *ens, const void *q, void *work, const char *cache_pa
     for (int l : {DG_KERNEL_LINE, DG_KERNEL_HALF}) {
       lay[o] = l;
       float ms = 0.f;
-      if ((rc = set_layouts(lay)) != DG_OK || (rc = upload_schedule(ens, 4, 0, 0)) != DG_OK ||
+      if ((rc = set_layouts(lay)) != DG_OK || (rc = upload_schedule(ens, 1, 0, 0)) != DG_OK ||
           (rc = time_two_stages(&ms)) != DG_OK)
         break;
       if (ms < best) {
@@ -574,7 +575,7 @@ int dg_ens_autotune(dg_ens *ens, const void *q, void *work, const char *cache_pa
   //    or 4 wavefronts per workgroup
   const int n_items = (int)ens->items.size();
   float best = 1e30f;
-  int best_w = 4, best_p = 0, best_f = 0;
+  int best_w = 1, best_p = 0, best_f = 0;
   for (int f : {0, 1}) {
     if (rc != DG_OK) break;
     if (f == 1 && !all_line(ens)) continue;
