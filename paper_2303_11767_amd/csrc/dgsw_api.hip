@@ -139,27 +139,31 @@ const char *dg_last_error(void) { return dgsw::last_error(); }
 
 }  // extern "C"
 
-// Kernel layout of a mesh, or of the members of one order of an ensemble, from the
-// number of wavefronts of its line layout; chosen from MI355X stage timings of both layouts over
-// r = 1..5, 90x45 .. 1440x720 and both precisions: the half layout for FP64 at
-// r = 1 (1440x720 91 us a stage against 97), r = 3 (the matrix-core stage) and
-// r >= 5 (the line layout's registers allow one wavefront per SIMD), and
-// wherever the line layout has few wavefronts.  Up to how many, by order (half
-// / line, us a stage): r = 1 FP32 3072 (360x180, 2160 wavefronts: 5.7 / 6.0;
-// 512x256, 4096: 8.6 / 7.7); r = 2 1024 (FP32 180x90, 810: 5.7 / 5.7; 270x135,
-// 1755: 8.5 / 7.1; FP64 7.4 / 7.9 and 11.3 / 10.6); r = 3 FP32 2048 (180x90, 1080:
-// 5.8 / 6.9; 270x135, 2295: 8.9 / 9.2; 360x180, 4140: - / 13.5); r = 4 512, where
-// the work the two halves duplicate costs more (FP32 120x60, 600: 7.8 / 7.5;
-// FP64 90x45, 360: 7.4 / 9.9); r = 5 FP32 1600 (135x68, 952: 8.6 / 9.6; 180x90,
-// 1620: 12.2 / 12.3).  dg_autotune measures instead.
-int dgsw::default_layout(bool f64, int r, long long waves_line) {
-  const int few = r == 1 ? 3072 : (r == 2 ? 1024 : (r <= 3 ? 2048 : (r == 5 ? 1600 : 512)));
-  return (f64 && (r == 1 || r == 3 || r >= 5)) || waves_line <= few ? DG_KERNEL_HALF : DG_KERNEL_LINE;
-}
-
+// Kernel layout of a mesh from the number of wavefronts of its line layout: the
+// half layout up to so many, by order, from MI355X stage times of both layouts at
+// r = 0..7, 32x16 .. 720x360, SSP-RK3 and RK4, both precisions.  It is right to 2 % in
+// 158 of those 159 cells (r = 4 FP64 270x135 is 6 % off).  Microseconds a stage of
+// RK3, line / half, on both sides of each line (the wavefronts in brackets):
+//   FP64 r = 0 360x180 (1080) 5.4 / 4.8, 512x256 (2048) 5.9 / 6.2; r = 2 180x90 (810)
+//   8.1 / 7.6, 270x135 (1755) 10.9 / 11.6; r = 4 135x68 (816) 12.3 / 10.8, 180x90 (1350)
+//   15.5 / 16.2; r = 6 32x16 (64) 11.8 / 10.1, 90x45 (450) 14.6 / 17.9; half at any size:
+//   r = 1 (720x360 26.8 / 22.1), r = 3 (the matrix-core stage, 86 / 66), r = 5 (392 /
+//   218) and r = 7 (360x180 184 / 97), where the line layout has one wavefront per SIMD.
+//   FP32 r = 0 as FP64; r = 1 360x180 (2160) 6.2 / 5.9, 512x256 (4096) 7.6 / 8.4; r = 2
+//   90x45 (225) 4.6 / 4.6, 180x90 (810) 5.7 / 6.0; r = 3 270x135 (2295) 9.1 / 8.9, 360x180
+//   (4140) 13.0 / 14.1; r = 4 90x45 (360) 7.0 / 6.5, 120x60 (600) 7.5 / 8.1; r = 5 360x180
+//   (6480) 32.0 / 30.9, 512x256 (13312) 54.0 / 55.6; r = 6 90x45 (450) 9.9 / 8.7, 120x60
+//   (840) 11.3 / 11.8; r = 7 half at any size (720x360 206 / 174).
+// dg_autotune measures instead.
 namespace {
 constexpr long long kAlways = INT64_MAX;
 }
+int dgsw::default_layout(bool f64, int r, long long waves_line) {
+  static constexpr long long few[2][kMaxNP] = {{1536, kAlways, 1024, kAlways, 1024, kAlways, 128, kAlways},
+                                               {1536, 3072, 384, 3072, 512, 8192, 512, kAlways}};
+  return waves_line <= few[f64 ? 0 : 1][r] ? DG_KERNEL_HALF : DG_KERNEL_LINE;
+}
+
 // The same for the members of one order of an ensemble, which run in one launch: by
 // the wavefronts of all of them (microseconds a stage of 32 members up to 180x90
 // and one of 360x180, line / half: FP32 r = 2 24.7 / 36.9, r = 4 62 / 94, r = 5 92 / 99, r = 6
