@@ -59,11 +59,13 @@ namespace dgsw {
 // fewest bank conflicts over the stage's accesses among those up to 28 values
 // (r = 1, whose unpadded stride makes most of its LDS accesses wait eight times:
 // stage times before and after at 720x360, FP64 half 29.9 / 23.5 us and line 36.8 /
-// 27.4, FP32 18.0 / 14.6 and 19.2 / 13.5; other orders within 2 %).  0: none (the
-// half layout of r = 3 FP64 is the matrix-core stage of dgsw_stage_m4.hpp).
+// 27.4, FP32 18.0 / 14.6 and 19.2 / 13.5; r = 6 7 .. 10 %, other orders 1 .. 5 %).  0:
+// none (r = 5 FP32, whose 252 values are rows on 16 bytes: padded to 266, 360x180
+// dq/dt 29.9 -> 30.8 us and ensembles 2 .. 4 %; the half layout of r = 3 FP64 is the
+// matrix-core stage of dgsw_stage_m4.hpp).
 template <typename T>
 constexpr int lds_stride(int np, int used, bool half) {
-  constexpr int line32[9] = {0, 21, 50, 81, 120, 185, 266, 347, 436}, line64[9] = {0, 21, 50, 81, 122, 185, 260, 340, 434};
+  constexpr int line32[9] = {0, 21, 50, 81, 120, 185, 0, 347, 436}, line64[9] = {0, 21, 50, 81, 122, 185, 260, 340, 434};
   constexpr int half32[9] = {0, 22, 52, 101, 152, 217, 298, 392, 492}, half64[9] = {0, 22, 52, 92, 0, 217, 264, 392, 434};
   const int padded =
       np > 8 ? 0 : (sizeof(T) == 4 ? (half ? half32[np] : line32[np]) : (half ? half64[np] : line64[np]));
