@@ -86,6 +86,7 @@ struct EnsLaunch {
   const int *bounds;    // parts + 1 item offsets, one contiguous range per workgroup
   int parts, combine;
   int flat;             // one item per wavefront over [begin, end) (per-order launches)
+  int large;            // the three states of a stage exceed the Infinity Cache
   int begin, end;
   double c0, c1;
 };

@@ -7,22 +7,31 @@ namespace dgsw {
 
 // ------------------------------------------------------------------ ensemble
 // What a line stage takes in the kernel over all orders (kFused), the persistent
-// kernel of one order and the flat one.  An item is short and comes with loads of
-// its own, so strips and freely moved table loads pay less often than in a mesh.
-// Microseconds a stage of 32 members 33x17 .. 180x90 and one of 360x180, FP32:
+// kernel of one order and the flat one (kFlat; kFlatLarge: of an ensemble whose
+// states, read and written, exceed the Infinity Cache).  An item is short and comes
+// with loads of its own, so strips and freely moved table loads pay less often than
+// in a mesh, strips at r = 2 and 5 only where memory is the limit.  Microseconds a
+// stage of 32 members 33x17 .. 180x90 and one of 360x180, FP32:
 //   strips / rows           r = 1        2            4            5            6
 //     flat              14.2 / 14.6  25.8 / 24.7  62.7 / 72.0  95.1 / 93.9  138.8 / 147.1
 //     persistent        14.3 / 14.3  28.9 / 27.3  84.1 / 82.4   122 / 113    164 / 154
 //   (8 members, r = 4 persistent with two wavefronts 20.0 / 19.8, r = 1 6.2 / 5.8)
-//   tables moved freely / in order: r = 5 flat 93.9 / 92.4, r = 7 flat 187 / 179,
+//   flat, members 90x45 .. 360x180, by the packed state: r = 2 82 MB 68.0 / 65.2,
+//     109 MB 90.4 / 96.7, 164 MB 139 / 157; r = 5 52 MB 57.0 / 55.7, 105 MB 105.5 /
+//     106.7, 210 MB 221 / 226, 630 MB 580 / 611
+//   tables moved freely / in order: r = 5 rows 93.9 / 92.4, r = 7 flat 187 / 179,
 //     persistent 186 / 193
 // In the fused kernel both cost a wavefront per SIMD and a hundred spilled scalars
 // (64 members 1.75 -> 2.4 ms a step).
-enum { kFused, kPersistent, kFlat };
+enum { kFused, kPersistent, kFlat, kFlatLarge };
 template <typename T, int NP, int FORM>
-constexpr bool ens_strips = sizeof(T) == 4 && ((NP == 5 && FORM != kFused) || ((NP == 2 || NP == 7) && FORM == kFlat));
+constexpr bool ens_strips = sizeof(T) == 4 && ((NP == 5 && FORM != kFused) || ((NP == 2 || NP == 7) && FORM >= kFlat) ||
+                                               ((NP == 3 || NP == 6) && FORM == kFlatLarge));
 template <typename T, int NP, int FORM>
-constexpr bool ens_moved = sizeof(T) == 4 && FORM != kFused && NP != 6 && !(NP == 8 && FORM == kFlat);
+constexpr bool ens_moved = sizeof(T) == 4 && FORM != kFused && (NP != 6 || FORM == kFlatLarge) && !(NP == 8 && FORM == kFlat);
+// the orders whose flat kernel has the two forms
+template <typename T, int NP, int LAY>
+constexpr bool ens_two_flat = LAY == 0 && ens_strips<T, NP, kFlat> != ens_strips<T, NP, kFlatLarge>;
 // Wavefronts a SIMD: r = 6 FP32 in strips needs a few registers more than three
 // allow (148.4 -> 138.8 us; the persistent kernel would spill, 164 -> 221).  The
 // matrix-core items hold 113 .. 122 registers and 22 accumulation registers, so
@@ -194,38 +203,45 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage_np(const T *__restrict__
 // Flat form: workgroup b takes items begin + b*WPB + wv, one item per
 // wavefront, so the hardware schedules the ensemble like an ordinary grid
 // (no loop: same register budget as the single-mesh kernel).
-template <typename T, int NP, int LAY, int WPB, int CM>
+template <typename T, int NP, int LAY, int WPB, int CM, int FORM>
 __global__ __attribute__((amdgpu_waves_per_eu(ens_flat_waves<T, NP, LAY>)))
 __launch_bounds__(64 * WPB) void k_ens_stage_flat(const T *__restrict__ q, const T *q0, T *out,
                                                              const unsigned char *__restrict__ tabs,
                                                              const EnsItem *__restrict__ items,
                                                              int begin, int end, int combine, T c0, T ce) {
-  __shared__ T tab_all[WPB][EnsLds<T, NP, LAY, kFlat>::TB];
-  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY, kFlat>::SH];
+  __shared__ T tab_all[WPB][EnsLds<T, NP, LAY, FORM>::TB];
+  __shared__ __attribute__((aligned(16))) T sh_all[WPB][EnsLds<T, NP, LAY, FORM>::SH];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int it = begin + xcd_block(blockIdx.x, gridDim.x) * WPB + wv;
   if (it >= end) return;
   const EnsItem m = items[it];
-  ens_item<T, NP, LAY, CM, kFlat>(m, tabs, q, q0, out, combine, c0, ce, lane, tab_all[wv], sh_all[wv]);
+  ens_item<T, NP, LAY, CM, FORM>(m, tabs, q, q0, out, combine, c0, ce, lane, tab_all[wv], sh_all[wv]);
 }
 
 // the combination mode is a template parameter of the ensemble kernels too:
 // 0 (right-hand side) or 1 (Shu-Osher stage)
-template <typename T, int NP, int LAY, int WPB>
-static hipError_t launch_ens_flat_t(const EnsLaunch &a, hipStream_t s) {
+template <typename T, int NP, int LAY, int WPB, int FORM>
+static hipError_t launch_ens_flat_f(const EnsLaunch &a, hipStream_t s) {
   const int n = a.end - a.begin;
   const dim3 grid((n + WPB - 1) / WPB), block(64 * WPB);
   if (a.combine)
-    hipLaunchKernelGGL((k_ens_stage_flat<T, NP, LAY, WPB, 1>), grid, block, 0, s, static_cast<const T *>(a.q),
+    hipLaunchKernelGGL((k_ens_stage_flat<T, NP, LAY, WPB, 1, FORM>), grid, block, 0, s, static_cast<const T *>(a.q),
                        static_cast<const T *>(a.q0), static_cast<T *>(a.out),
                        static_cast<const unsigned char *>(a.tabs), a.items, a.begin, a.end, 1, T(a.c0),
                        T(a.c0 + a.c1 - 1.0));
   else
-    hipLaunchKernelGGL((k_ens_stage_flat<T, NP, LAY, WPB, 0>), grid, block, 0, s, static_cast<const T *>(a.q),
+    hipLaunchKernelGGL((k_ens_stage_flat<T, NP, LAY, WPB, 0, FORM>), grid, block, 0, s, static_cast<const T *>(a.q),
                        static_cast<const T *>(a.q0), static_cast<T *>(a.out),
                        static_cast<const unsigned char *>(a.tabs), a.items, a.begin, a.end, 0, T(a.c0),
                        T(a.c0 + a.c1 - 1.0));
   return hipGetLastError();
+}
+
+template <typename T, int NP, int LAY, int WPB>
+static hipError_t launch_ens_flat_t(const EnsLaunch &a, hipStream_t s) {
+  if constexpr (ens_two_flat<T, NP, LAY>)
+    if (a.large) return launch_ens_flat_f<T, NP, LAY, WPB, kFlatLarge>(a, s);
+  return launch_ens_flat_f<T, NP, LAY, WPB, kFlat>(a, s);
 }
 
 template <typename T, int NP, int LAY, int WPB>

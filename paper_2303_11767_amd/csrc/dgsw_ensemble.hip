@@ -230,6 +230,7 @@ int ens_stage(dg_ens *e, const void *q, const void *q0, void *out, int combine, 
   a.c0 = c0;
   a.c1 = c1;
   a.flat = 0;
+  a.large = 3 * e->off[e->n] * (int64_t)e->elem_bytes > (int64_t)256 << 20;   // (MI355X: 256 MiB)
   a.begin = a.end = 0;
   if (e->fused) {
     a.bounds = e->d_bounds;
