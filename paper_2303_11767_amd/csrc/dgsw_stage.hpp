@@ -363,7 +363,6 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
   const glob_p gt = (glob_p)A.gt;
   const int n_lon = A.n_lon, n_lat = A.n_lat;
   constexpr int combine = CM;
-  const T c0 = A.c0, c1 = A.c1, dt = A.dt;
   int g = lane / NP, t = lane - g * NP;
   const bool idle = g >= GPW;          // the 64 mod NP spare lanes: a dummy LDS slot
   if (idle) { g = GPW; t = lane - GPW * NP; }
@@ -625,7 +624,7 @@ __device__ __forceinline__ void stage_wave(const StageArgs<T, NP> &A, const int 
 
   // ---- the epilogue's operands (rows), loaded late to keep registers free: q
   // (again, from cache), q^n and the forcing
-  const bool use_q0 = combine == 2 || (combine == 1 && c0 != T(0));
+  const bool use_q0 = combine == 2 || (combine == 1 && A.c0 != T(0));
   T q0r[3][NP], fr[3][NP], res[3][NP];
 #pragma unroll
   for (int v = 0; v < 3 && !STRIPS; ++v) {
