@@ -65,8 +65,9 @@ __global__ __attribute__((amdgpu_waves_per_eu(MORE ? 3 : 4))) __launch_bounds__(
 // itself takes a few registers more than the LDS would let run: r = 6 FP32 171
 // registers and two instead of three (360x180 49.1 -> 45.4 us a stage, 720x360
 // 166 -> 156), r = 4 FP64 dq/dt 257 and one instead of two (56 -> 43 us at
-// 360x180).  Elsewhere the limit costs more in spills than it brings (r = 5 FP32
-// 36 us with three, 43 with four; r = 4 FP64 with a combination 45 and 49).
+// 360x180).  Elsewhere the limit costs more in spills than it brings (r = 5 FP32,
+// three by itself, held to four 36 -> 43 us; r = 4 FP64 with a combination, held to
+// two, 45 -> 49).
 template <typename T, int NP, int CM, bool STRIPS>
 constexpr int stage_waves() {
   if (!STRIPS) return 1;
