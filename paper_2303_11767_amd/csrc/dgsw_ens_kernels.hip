@@ -33,12 +33,13 @@ constexpr bool ens_moved = sizeof(T) == 4 && FORM != kFused && (NP != 6 || FORM 
 template <typename T, int NP, int LAY>
 constexpr bool ens_two_flat = LAY == 0 && ens_strips<T, NP, kFlat> != ens_strips<T, NP, kFlatLarge>;
 // Wavefronts a SIMD: r = 6 FP32 in strips needs a few registers more than three
-// allow (148.4 -> 138.8 us; the persistent kernel would spill, 164 -> 221).  The
+// allow (148.4 -> 138.8 us; the persistent kernel would spill, 164 -> 221; with four
+// wavefronts a workgroup the LDS allows two).  The
 // matrix-core items hold 113 .. 122 registers and 22 accumulation registers, so
 // three; held to four, flat items take 54.7 us for 55.2 and persistent ones spill
 // (81 for 73).
-template <typename T, int NP, int LAY>
-constexpr int ens_flat_waves = sizeof(T) == 4 && NP == 7 && LAY == 0 ? 3 : 1;
+template <typename T, int NP, int LAY, int WPB>
+constexpr int ens_flat_waves = sizeof(T) == 4 && NP == 7 && LAY == 0 && WPB < 4 ? 3 : 1;
 // LDS of one wavefront for any order up to NPMAX (the fused kernel)
 template <typename T, int NPMAX>
 struct LdsMax {
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(64 * WPB) void k_ens_stage_np(const T *__restrict__
 // wavefront, so the hardware schedules the ensemble like an ordinary grid
 // (no loop: same register budget as the single-mesh kernel).
 template <typename T, int NP, int LAY, int WPB, int CM, int FORM>
-__global__ __attribute__((amdgpu_waves_per_eu(ens_flat_waves<T, NP, LAY>)))
+__global__ __attribute__((amdgpu_waves_per_eu(ens_flat_waves<T, NP, LAY, WPB>)))
 __launch_bounds__(64 * WPB) void k_ens_stage_flat(const T *__restrict__ q, const T *q0, T *out,
                                                              const unsigned char *__restrict__ tabs,
                                                              const EnsItem *__restrict__ items,
