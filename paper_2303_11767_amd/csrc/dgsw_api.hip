@@ -141,26 +141,28 @@ const char *dg_last_error(void) { return dgsw::last_error(); }
 
 // Kernel layout of a mesh from the number of wavefronts of its line layout: the
 // half layout up to so many, by order, from MI355X stage times of both layouts at
-// r = 0..7, 32x16 .. 720x360, SSP-RK3 and RK4, both precisions.  It is right to 2 % in
-// 158 of those 159 cells (r = 4 FP64 270x135 is 6 % off).  Microseconds a stage of
-// RK3, line / half, on both sides of each line (the wavefronts in brackets):
-//   FP64 r = 0 360x180 (1080) 5.4 / 4.8, 512x256 (2048) 5.9 / 6.2; r = 2 180x90 (810)
-//   8.1 / 7.6, 270x135 (1755) 10.9 / 11.6; r = 4 135x68 (816) 12.3 / 10.8, 180x90 (1350)
-//   15.5 / 16.2; r = 6 32x16 (64) 11.8 / 10.1, 90x45 (450) 14.6 / 17.9; half at any size:
-//   r = 1 (720x360 26.8 / 22.1), r = 3 (the matrix-core stage, 86 / 66), r = 5 (392 /
-//   218) and r = 7 (360x180 184 / 97), where the line layout has one wavefront per SIMD.
-//   FP32 r = 0 as FP64; r = 1 360x180 (2160) 6.2 / 5.9, 512x256 (4096) 7.6 / 8.4; r = 2
-//   90x45 (225) 4.6 / 4.6, 180x90 (810) 5.7 / 6.0; r = 3 270x135 (2295) 9.1 / 8.9, 360x180
-//   (4140) 13.0 / 14.1; r = 4 90x45 (360) 7.0 / 6.5, 120x60 (600) 7.5 / 8.1; r = 5 360x180
-//   (6480) 32.0 / 30.9, 512x256 (13312) 54.0 / 55.6; r = 6 90x45 (450) 9.9 / 8.7, 120x60
-//   (840) 11.3 / 11.8; r = 7 half at any size (720x360 206 / 174).
+// r = 0..7, 32x16 .. 720x360, SSP-RK3 and RK4, both precisions, and ten more sizes
+// about each line.  It is right to 3 % in 263 of those 269 cells, to 7 % in all (a
+// row's last wavefront is more or less full, which one number does not tell).
+// Microseconds a stage, line / half, on both sides of each line (the wavefronts in
+// brackets):
+//   FP64 r = 0 (1386) 5.7 / 5.5, (1470) 5.7 / 5.8; r = 2 (980) 8.5 / 8.1, (1040) 9.2 /
+//   9.6; r = 4 (1014) 13.4 / 12.3, (1148) 15.4 / 15.7; r = 6 (105) 12.4 / 11.7, (138)
+//   12.5 / 13.2; half at any size: r = 1 (720x360 26.8 / 22.1), r = 3 (the matrix-core
+//   stage, 86 / 66), r = 5 (392 / 218) and r = 7 (360x180 184 / 97), where the line
+//   layout has one wavefront per SIMD.
+//   FP32 r = 0 (1386) 4.3 / 4.3, (1554) 4.4 / 4.7; r = 1 (2148) 6.2 / 6.1, (2574) 6.5 /
+//   6.6; r = 2 (225) 4.8 / 4.8, (255) 4.7 / 5.1; r = 3 (2520) 9.6 / 9.2, (2831) 9.6 /
+//   10.2; r = 4 (550) 7.6 / 7.3, (580) 7.7 / 8.3; r = 5 (4147) 23.3 / 21.7, (5120) 25.3 /
+//   25.7; r = 6 (600) 10.9 / 10.6, (960) 11.9 / 12.2; r = 7 half at any size (720x360
+//   206 / 174).
 // dg_autotune measures instead.
 namespace {
 constexpr long long kAlways = INT64_MAX;
 }
 int dgsw::default_layout(bool f64, int r, long long waves_line) {
-  static constexpr long long few[2][kMaxNP] = {{1536, kAlways, 1024, kAlways, 1024, kAlways, 128, kAlways},
-                                               {1536, 3072, 384, 3072, 512, 8192, 512, kAlways}};
+  static constexpr long long few[2][kMaxNP] = {{1400, kAlways, 1024, kAlways, 1024, kAlways, 128, kAlways},
+                                               {1400, 2400, 240, 2560, 560, 4608, 640, kAlways}};
   return waves_line <= few[f64 ? 0 : 1][r] ? DG_KERNEL_HALF : DG_KERNEL_LINE;
 }
 
