@@ -75,13 +75,13 @@ __device__ __forceinline__ float gelu_and_grad(float &z) {
 // the LDS rows the B operand, so every lane ends with 4 consecutive units of
 // one row and writes them as one 8-byte LDS store.  Rounding points: BF16
 // inputs, weights and hidden activations, FP32 accumulation, bias and GELU in
-// FP32.  Bound by the vector unit (GELU: 14 instructions per unit and row,
-// 45 k of the 72 k cycles; the matrix cores are busy for 13 k and the weights'
-// first load takes about 10 k).  Inputs have a buffer of their own, so a tile
-// has three barriers and the next tile's operands are fetched meanwhile: with
-// the operands fetched at the tile's start and rows padded instead of permuted
-// 40.0 us for 64 800 rows, now 35.9 (36.8 before the weights were requested
-// behind the first tile's inputs); weights streamed from L2 for two
+// FP32.  By its counters the vector unit is busy 0.47 of the time (most of it the
+// GELU, 14 instructions per unit and row), the matrix cores 0.14, and 0.30 of the
+// wavefronts' time waits for memory or a barrier.  Inputs have a buffer of their
+// own, so a tile has three barriers and the next tile's operands are fetched
+// meanwhile: with the operands fetched at the tile's start and rows padded instead
+// of permuted 40.0 us for 64 800 rows, now 35.6 (36.8 before the weights were
+// requested behind the first tile's inputs); weights streamed from L2 for two
 // workgroups per CU took 38.8.
 constexpr int kRows = 64;                 // rows per tile
 constexpr int kMlpGrid = 256;             // persistent workgroups: one per MI355X compute unit
@@ -278,7 +278,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(2, 2))) __launch_bounds__(64 * kWa
 #pragma unroll
     for (int vm = 0; vm < 12; ++vm) raw[vm] = src[vm];
     if (FROM_Q ? (wv >= 1 && wv <= kExtra) : wv == kExtra) {
-      const In *p0, *p1;
+      const In *p0 = nullptr, *p1 = nullptr;
       if (wv == kExtra) {
         p0 = task_src(e0n, lane + 64 * kWaves);
         p1 = p0 + 6;
@@ -535,10 +535,11 @@ hipError_t launch_prep_weights(const float *P, const PrepWeights &w, hipStream_t
 //                   gradient, split over ranges of rows;
 //   k_train_update  the ranges' sums in order, and Adam.
 // The 29 launches this replaces (one GEMM, conversion, column sum or copy
-// each) took 157 us at 8192 rows, launches and memory round trips almost all of
-// it; these take 33.1 (rows 19.5, one tile per CU: a serial chain of five
-// products and their barriers, 27 k cycles; gradients 8.9, update 5.4, weights
-// 3).  Rounding points as before: BF16 factors of every product, FP32
+// each) took 156 us at 8192 rows, launches and memory round trips almost all of
+// it; these take 33.7.  Under the tracer, which lengthens every launch: rows 18.4
+// (one tile per CU: a serial chain of five products and their barriers; the vector
+// unit busy 0.23 of the time, waiting 0.49), gradients 9.2, update 5.3, weights 3.4.
+// Rounding points as before: BF16 factors of every product, FP32
 // accumulation, bias, GELU, loss and gradients in FP32.
 constexpr int kTrRows = 32;               // rows of a tile: one K block of the weight gradients
 constexpr int kLdX = kInPad + 8, kLdY = kOutPad + 8;   // LDS row strides in BF16
