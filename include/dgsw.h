@@ -71,7 +71,8 @@ enum {
   DG_OK = 0,
   DG_EINVAL = -1,       /* bad argument: null, misaligned, out of range     */
   DG_EDTYPE = -2,       /* dtype not DG_F64 / DG_F32                          */
-  DG_ENOMEM = -3,       /* device allocation of the context tables failed     */
+  DG_ENOMEM = -3,       /* allocation of the context tables (or, in dg_mass,
+                           of pinned memory for its result) failed            */
   DG_EHIP = -4,         /* a HIP runtime call or kernel launch failed         */
   DG_ENONFINITE = -5,   /* dg_mass found a NaN or Inf in the state            */
   DG_EUNSUPPORTED = -6  /* valid but not supported (e.g. order > 7)           */

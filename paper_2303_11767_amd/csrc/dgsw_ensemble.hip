@@ -302,9 +302,9 @@ int dg_ens_init(const dg_mesh_desc *members, int32_t n_members, void *hip_stream
     least = waves_line[c->np - 1] == 0 ? w : std::min(least, w);
     waves_line[c->np - 1] += w;
   }
-  // the members of an order run in one launch, so they take the layout of a mesh
-  // with all of their wavefronts (by each member's own size, small members kept
-  // the half layout: FP32 ensembles of 64 / 16 / 6 members 1003 / 295 / 161 us a
+  // the members of an order run in one launch, so they take a layout by all of
+  // their wavefronts together (by each member's own size, small members kept the
+  // half layout: FP32 ensembles of 64 / 16 / 6 members 1003 / 295 / 161 us a
   // step against 918 / 248 / 130, 24 in FP64 771 against 729)
   for (const dg_ctx *c : e->members)
     e->layout.push_back(
